@@ -1465,8 +1465,9 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     // OUT elements: 2x2x2 Gauss points
     a.n_items = c->n_std;
     a.items = c->d_std;
-    if (fp64) vmsk::launch_assemble_f64(ms, a, false, mat);
-    else vmsk::launch_assemble_mixed(ms, a, false, mat, c->prm.precision == VMS_MIXED_FP16);
+    if (!mat) vmsk::launch_residual(ms, a, false, fp64, nullptr);
+    else if (fp64) vmsk::launch_assemble_f64(ms, a, false);
+    else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[3], ms));
     int late_rc = VMS_OK;
@@ -1485,8 +1486,9 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         a.pt_cnt = c->d_sub_cnt;
         a.entries = c->d_entries;
         a.slot0 = c->n_std;
-        if (fp64) vmsk::launch_assemble_f64(ls, a, true, mat, items_cap);
-        else vmsk::launch_assemble_mixed(ls, a, true, mat, c->prm.precision == VMS_MIXED_FP16, items_cap);
+        if (!mat) vmsk::launch_residual(ls, a, true, fp64, nullptr);
+        else if (fp64) vmsk::launch_assemble_f64(ls, a, true, items_cap);
+        else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, items_cap);
         HIPCHK(c, hipGetLastError());
     }
     if (late_rc == VMS_OK && c->wbc && c->n_surf_items) {
@@ -1611,7 +1613,7 @@ static int jv_impl(vms_ctx *c, const double *const fp[7], const double *x, doubl
     if (tm) HIPCHK(c, hipEventRecord(c->ev[2], c->stream));
     a.n_items = c->n_std;
     a.items = c->d_std;
-    vmsk::launch_jacobian_action(c->stream, a, false, fp64, x);
+    vmsk::launch_residual(c->stream, a, false, fp64, x);
     HIPCHK(c, hipGetLastError());
     if (tm) HIPCHK(c, hipEventRecord(c->ev[3], c->stream));
     if (c->n_sub_items) {
@@ -1621,7 +1623,7 @@ static int jv_impl(vms_ctx *c, const double *const fp[7], const double *x, doubl
         a.pt_cnt = c->d_sub_cnt;
         a.entries = c->d_entries;
         a.slot0 = c->n_std;
-        vmsk::launch_jacobian_action(c->stream, a, true, fp64, x);
+        vmsk::launch_residual(c->stream, a, true, fp64, x);
         HIPCHK(c, hipGetLastError());
     }
     if (c->wbc && c->n_surf_items) {

@@ -803,14 +803,6 @@ __global__ VMS_ASM_BOUNDS(MODE) void k_asm2(AsmArgs a) {
     }
 }
 
-// Jacobian action y = J x along x (the residual output of a receives y)
-template <typename T, bool SUB>
-__global__ VMS_ASM_BOUNDS(1) void k_asm2_jv(AsmArgs a, const double *x) {
-    constexpr int MODE = sizeof(T) == 8 ? 0 : 1;
-    __shared__ Smem<T, MODE == 0 ? 4 : 8, false, 11> sm;
-    asm_item<T, MODE, SUB, false, MODE == 0 ? 4 : 8, true>(a, blockIdx.x, sm, x);
-}
-
 // Persistent form over many contexts: every workgroup takes units of work
 // from a device counter until none is left, in the order of the unit list
 // (heaviest first); a unit is a run of OUT elements or of sub-cell work items
@@ -1059,52 +1051,30 @@ int sub_items_per_cu(int precision) {
     return n;
 }
 
-void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, bool mat, int wg_per_cu) {
+void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, int wg_per_cu) {
     if (a.n_items <= 0) return;
     dim3 grid((unsigned)(sub ? a.n_items : (a.n_items + 1) / 2)), block(64);
-    if (!sub) {
-        if (mat) hipLaunchKernelGGL((k_asm2<double, 0, false, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_asm2<double, 0, false, false>), grid, block, 0, s, a);
-    } else {
-        if (mat) {
-            const size_t dyn = lds_for_cap((const void *)&k_asm2<double, 0, true, true>, wg_per_cu);
-            hipLaunchKernelGGL((k_asm2<double, 0, true, true>), grid, block, dyn, s, a);
-        } else {
-            hipLaunchKernelGGL((k_asm2<double, 0, true, false>), grid, block, 0, s, a);
-        }
-    }
+    if (sub)
+        hipLaunchKernelGGL((k_asm2<double, 0, true, true>), grid, block,
+                           lds_for_cap((const void *)&k_asm2<double, 0, true, true>, wg_per_cu), s, a);
+    else
+        hipLaunchKernelGGL((k_asm2<double, 0, false, true>), grid, block, 0, s, a);
 }
 
-void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, bool mat, int fp16, int wg_per_cu) {
+void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, int fp16, int wg_per_cu) {
     if (a.n_items <= 0) return;
     dim3 grid((unsigned)(sub ? a.n_items : (a.n_items + 1) / 2)), block(64);
-#define VMS_L(MODE)                                                                              \
-    do {                                                                                         \
-        if (!sub) {                                                                              \
-            if (mat) hipLaunchKernelGGL((k_asm2<float, MODE, false, true>), grid, block, 0, s, a); \
-            else hipLaunchKernelGGL((k_asm2<float, MODE, false, false>), grid, block, 0, s, a);    \
-        } else {                                                                                 \
-            if (mat) hipLaunchKernelGGL((k_asm2<float, MODE, true, true>), grid, block,            \
-                                        lds_for_cap((const void *)&k_asm2<float, MODE, true, true>, \
-                                                    wg_per_cu), s, a);                             \
-            else hipLaunchKernelGGL((k_asm2<float, MODE, true, false>), grid, block, 0, s, a);     \
-        }                                                                                        \
+#define VMS_L(MODE)                                                                             \
+    do {                                                                                        \
+        if (sub)                                                                                \
+            hipLaunchKernelGGL((k_asm2<float, MODE, true, true>), grid, block,                  \
+                               lds_for_cap((const void *)&k_asm2<float, MODE, true, true>, wg_per_cu), s, a); \
+        else                                                                                    \
+            hipLaunchKernelGGL((k_asm2<float, MODE, false, true>), grid, block, 0, s, a);       \
     } while (0)
     if (fp16) VMS_L(2);
     else VMS_L(1);
 #undef VMS_L
-}
-
-void launch_jacobian_action(hipStream_t s, const AsmArgs &a, bool sub, bool fp64, const double *x) {
-    if (a.n_items <= 0) return;
-    dim3 grid((unsigned)a.n_items), block(64);
-    if (fp64) {
-        if (sub) hipLaunchKernelGGL((k_asm2_jv<double, true>), grid, block, 0, s, a, x);
-        else hipLaunchKernelGGL((k_asm2_jv<double, false>), grid, block, 0, s, a, x);
-    } else {
-        if (sub) hipLaunchKernelGGL((k_asm2_jv<float, true>), grid, block, 0, s, a, x);
-        else hipLaunchKernelGGL((k_asm2_jv<float, false>), grid, block, 0, s, a, x);
-    }
 }
 
 }  // namespace vmsk

@@ -162,7 +162,7 @@ inline void set_params(AsmArgs &a, double rho, double mu, double dt, double thet
 // wg_per_cu > 0 (sub-cell items only): dynamic LDS so that at most that many
 // workgroups share a CU, leaving the rest of its waves to another stream's
 // kernel
-void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, bool mat, int wg_per_cu = 0);
+void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, int wg_per_cu = 0);
 
 // one unit of the persistent batched assembly: items [first, first + count) of
 // tree `tree`'s OUT-element list (sub = 0) or sub-cell work-item list (sub = 1)
@@ -178,7 +178,7 @@ struct BatchUnit {
 void launch_assemble_batch(hipStream_t s, int precision, const AsmArgs *std_args,
                            const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
                            unsigned long long *counter, int n_groups);
-void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, bool mat, int fp16, int wg_per_cu = 0);
+void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, int fp16, int wg_per_cu = 0);
 // resident workgroups per CU of the sub-cell item kernel of a precision form
 // (0 FP64, 1 BF16x3, 2 FP16x2; with the matrix), from its registers and LDS
 int sub_items_per_cu(int precision);
@@ -268,9 +268,10 @@ struct SurfArgs {
 // Jacobian action along x into the residual records; fp64 selects FP64
 // element-matrix records (else FP32)
 void launch_surface(hipStream_t s, const SurfArgs &a, int mode, bool fp64, const double *x);
-// Jacobian action along x: FP64 point work if fp64, else FP32; the residual
-// records receive the element contributions to y
-void launch_jacobian_action(hipStream_t s, const AsmArgs &a, bool sub, bool fp64, const double *x);
+// Residual (x null) or Jacobian action along x without a matrix: FP64 point
+// work if fp64, else FP32; the residual records receive the element
+// contributions
+void launch_residual(hipStream_t s, const AsmArgs &a, bool sub, bool fp64, const double *x);
 // residual (or Jacobian action) from the residual records: out[4 n + i] = sum,
 // over node n's entries rlist[roff[n] .. roff[n + 1]) (8 record + slot,
 // ascending), of rrec[32 record + 4 slot + i]; 0 for a node without entries
