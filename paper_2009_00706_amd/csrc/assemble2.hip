@@ -34,9 +34,10 @@
 // as FP32.
 //
 // One 64-lane workgroup per element, points in chunks of 8.
-#include "geom.h"
-#include "kernels.h"
+#include "item_dev.h"
 #include "vms_point.h"
+
+#include <type_traits>
 
 namespace vmsk {
 using namespace vmsd;
@@ -47,43 +48,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-
-__device__ inline const double *field_in(const AsmArgs &a, int f) {
-    switch (f) {
-        case 0: return a.f[0];
-        case 1: return a.f[1];
-        case 2: return a.f[2];
-        case 3: return a.f[3];
-        case 4: return a.f[4];
-        case 5: return a.f[5];
-        default: return a.f[6];
-    }
-}
-
-// reference coordinates (double) and weight of point pt of the item
-template <bool SUB>
-__device__ inline void point_xw(const AsmArgs &a, uint32_t en, int pt, double h, double xi[3],
-                                double &w) {
-    if (!SUB) {
-        for (int k = 0; k < 3; ++k) xi[k] = ((pt >> k) & 1) ? VMS_XI : -VMS_XI;
-        const double hh = 0.5 * h;
-        w = hh * hh * hh;
-        return;
-    }
-    const int l = (int)(en & 3u), D = a.depth;
-    const uint32_t key = en >> 2;
-    const int gp = (int)((key >> (3 * (D - l))) & 7u);
-    const double sl = ldexp(1.0, -l);
-    for (int ax = 0; ax < 3; ++ax) {
-        double f = 0.0;
-        for (int k = 1; k <= l; ++k)
-            if ((key >> (3 * (D - k + 1) + ax)) & 1u) f += ldexp(1.0, -k);
-        f = __dadd_rn(f, sl * (((gp >> ax) & 1) ? VMS_GP : VMS_GM));
-        xi[ax] = __dsub_rn(2.0 * f, 1.0);
-    }
-    const double hs = h * ldexp(1.0, -(l + 1));
-    w = hs * hs * hs;
-}
 
 // split x into three bf16 terms with x ~= h + m + l
 __device__ inline void split3(float x, __bf16 &h, __bf16 &m, __bf16 &l) {
@@ -118,21 +82,18 @@ __device__ inline void split2hx2(v2f x, v2h &h, v2h &l) {
 //   B(p, k, s)       constrained basis rows, point stride 40
 //   I(p, f, k)       interpolated fields, field stride 5, point stride 5 NF
 //   D(p, i, j, k, l) coefficient blocks, block stride 17, point stride 276
-// NF fields: the state (u, p, u_prev: 7), plus the direction (x_u, x_p: 4) in
-// the Jacobian action.
+// NF fields: the state (u, p, u_prev); the D blocks of all 8 points of a chunk are held at once
 constexpr int LU = 9, LB = 40, LDB = 17, LDP = 16 * LDB + 4;
-// PD = points whose D blocks are held at once (FP64: 4, mixed: 8); no D area
-// without the matrix
-template <typename T, int PD, bool MAT, int NF>
+template <typename T>
 struct Smem {
-    static constexpr int CP = 8;
+    static constexpr int CP = 8, PD = 8, NF = 7;
     T sU[NF * LU];
     T sC[8][8];
     T sB[CP * LB];
     T sQ[CP][NQ2];
     union {  // the interpolated fields are dead once the point quantities exist
         T sI[CP * NF * 5];
-        T sD[MAT ? PD * LDP : 1];  // weight folded in
+        T sD[PD * LDP];  // weight folded in
     };
     T sSc[CP];       // fp16 form: per-point bound of the contraction operands
     int sM[8];
@@ -143,10 +104,6 @@ struct Smem {
 #define SD(p, i, j, k, l) sD[(p) * LDP + ((i) * 4 + (j)) * LDB + (k) * 4 + (l)]
 
 
-// One work item (an element, or a run of sub-cell points of one element) by
-// one 64-lane workgroup. JV: the Jacobian action along the direction xd
-// (DEVICE, 4 n_nodes doubles, dof 4 node + c) instead of the residual, no
-// matrix.
 // Per-lane element data of one OUT work item, loaded ahead of its use: the
 // element, its level and hanging flag, the master of slot lane % 8, the
 // constraint weight code of (corner lane / 8, slot lane % 8) and, for lanes
@@ -177,15 +134,14 @@ __device__ inline void load_pre2(const AsmArgs &a, int64_t i0, int64_t i1, bool 
     P1.fv = (lane < 56 && P1.m >= 0) ? field_in(a, lane >> 3)[P1.m] : 0.0;
 }
 
-template <typename T, int MODE, bool SUB, bool MAT, int PD, bool JV = false>
-__device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
-                                         Smem<T, PD, MAT, JV ? 11 : 7> &sm,
-                                         const double *xd = nullptr, const ItemPre *pre = nullptr) {
+// One work item (an element, or a run of sub-cell points of one element) by
+// one 64-lane workgroup, mixed forms.
+template <typename T, int MODE, bool SUB>
+__device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item, Smem<T> &sm,
+                                         const ItemPre *pre = nullptr) {
     constexpr int CP = 8;  // points per chunk (one lane group of 8 per point)
-    constexpr int NF = JV ? 11 : 7;
-    static_assert(!(JV && MAT), "the Jacobian action has no matrix");
-    static_assert(MODE == 0 || PD == 8, "the mixed forms take 8 points per MFMA k-step");
-    static_assert(PD == 4 || PD == 8, "D blocks of 4 or 8 points at a time");
+    constexpr int PD = 8, NF = 7;
+    static_assert(MODE != 0, "FP64 element matrices: asm_item64");
     auto &sU = sm.sU;
     auto &sC = sm.sC;
     auto &sB = sm.sB;
@@ -208,7 +164,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
         const uint32_t code = pre ? pre->code : (a.ccode[4 * (int64_t)e + (bit >> 5)] >> (bit & 31)) & 3u;
         sC[v][s] = code == 3u ? T(1) : (code == 2u ? T(0.5) : (code == 1u ? T(0.25) : T(0)));
     }
-    if (pre && NF == 7) {
+    if (pre) {
         if (lane < 56) SU(lane >> 3, lane & 7) = (T)pre->fv;
         __syncthreads();
     } else {
@@ -216,7 +172,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
         for (int idx = lane; idx < NF * 8; idx += 64) {
             const int f = idx >> 3, s = idx & 7, m = sM[s];
             double v = 0.0;
-            if (m >= 0) v = f < 7 ? field_in(a, f)[m] : xd[4 * (int64_t)m + (f - 7)];
+            if (m >= 0) v = field_in(a, f)[m];
             SU(f, s) = (T)v;
         }
     }
@@ -234,21 +190,10 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
     const float hhalf = (float)(0.5 * hd), gh = (float)two_over_h;
     int s16 = INT_MAX;
 
-    // stage-2 accumulators and residual. FP64: 4x4x4 MFMA blocks (four per
-    // instruction, block = trial component j); lane l holds, for every (i, a
-    // half ah, b half bh), K^{ij}[4 ah + m][4 bh + n] with m = l / 16,
-    // j = (l / 4) % 4, n = l % 4. Mixed: 16x16 blocks (see phase 5).
-    double acc4[4][2][2];
+    // stage-2 accumulators (16x16 blocks, see phase 5) and residual
     v4f accf[8];
-    for (int i = 0; i < 4; ++i)
-        for (int h = 0; h < 4; ++h) acc4[i][h >> 1][h & 1] = 0.0;
     for (int t = 0; t < 8; ++t) accf[t] = v4f{0, 0, 0, 0};
     T R = T(0);  // lanes < 32: residual of (a = lane & 7, i = lane >> 3)
-    // FP64 with the matrix: the residual is one more 4x4x4 MFMA whose blocks
-    // 0 and 1 are the two halves of the rows a (columns i carry r^i[k]): lane
-    // l holds R[4 ((l / 4) % 4) + l / 16][l % 4] for (l / 4) % 4 < 2
-    constexpr bool RES_MFMA = MODE == 0 && MAT;
-    double accr = 0.0;
     // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
     const int64_t eoff = SUB ? a.pt_off[item] : 0;
     uint32_t en_cur = (SUB && (lane >> 3) < npts) ? a.entries[eoff + (lane >> 3)] : 0u;
@@ -294,9 +239,8 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
         }
         __syncthreads();
         // ---- phase 2: interpolation of the nodal fields (lane = (p, field))
-        constexpr int FL = NF > 8 ? 16 : 8;
-        for (int idx = lane; idx < CP * FL; idx += 64) {
-            const int p = idx / FL, f = idx % FL;
+        for (int idx = lane; idx < CP * 8; idx += 64) {
+            const int p = idx >> 3, f = idx & 7;
             if (p < np && f < NF) {
                 T v[4] = {T(0), T(0), T(0), T(0)};
                 for (int s = 0; s < 8; ++s) {
@@ -311,79 +255,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
         // point p evaluate the point state; lane r < 3 writes row / component
         // c = r of it and momentum row c of the residual coefficients r^i[k]
         // (times W), lane r = 3 the scalars and the continuity row.
-        if constexpr (JV) {
-            // Jacobian action: the same coefficients differentiated along the
-            // direction (fields 7..10: x_u, x_p at the new step) with tau_M,
-            // tau_C and taubar frozen at the state; d(u_theta) = theta x_u,
-            // d(a_t) = x_u / dt, d(p) = x_p
-            const int p = lane >> 3, r = lane & 7;
-            if (p < np && r < 4) {
-                T ut[3], gu[3][3], dut[3], dgu[3][3], dat[3];
-                for (int c = 0; c < 3; ++c) {
-                    ut[c] = th * SI(p, c, 0) + (T(1) - th) * SI(p, 4 + c, 0);
-                    dut[c] = th * SI(p, 7 + c, 0);
-                    dat[c] = SI(p, 7 + c, 0) * idt;
-                    for (int m = 0; m < 3; ++m) {
-                        gu[c][m] = th * SI(p, c, 1 + m) + (T(1) - th) * SI(p, 4 + c, 1 + m);
-                        dgu[c][m] = th * SI(p, 7 + c, 1 + m);
-                    }
-                }
-                T up[3], dup[3];
-                for (int c = 0; c < 3; ++c) {
-                    const T atc = (SI(p, c, 0) - SI(p, 4 + c, 0)) * idt;
-                    const T conv = ut[0] * gu[c][0] + ut[1] * gu[c][1] + ut[2] * gu[c][2];
-                    const T dconv = dut[0] * gu[c][0] + dut[1] * gu[c][1] + dut[2] * gu[c][2] +
-                                    ut[0] * dgu[c][0] + ut[1] * dgu[c][1] + ut[2] * dgu[c][2];
-                    up[c] = rho * (atc + conv) + SI(p, 3, 1 + c);
-                    dup[c] = rho * (dat[c] + dconv) + SI(p, 10, 1 + c);
-                }
-                const T s0 = tau0 + gG * (ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2]);
-                const T tauM = rsq<T>(s0);
-                const T tauC = h2_12 * s0 * tauM;
-                for (int c = 0; c < 3; ++c) {
-                    up[c] *= -tauM;
-                    dup[c] *= -tauM;
-                }
-                const T ddiv = dgu[0][0] + dgu[1][1] + dgu[2][2];
-                const T dpp = -rho * tauC * ddiv;
-                const T upg = gG * (up[0] * up[0] + up[1] * up[1] + up[2] * up[2]);
-                const T tb = upg > T(0) ? rsq<T>(upg) : T(0);
-                T *q = sQ[p];
-                const T W = q[QW];
-                if (r < 3) {
-                    // row c = r: its lane-indexed quantities come from LDS again
-                    const int c = r;
-                    T guc[3], dguc[3], dgcol[3];
-                    for (int m = 0; m < 3; ++m) {
-                        guc[m] = th * SI(p, c, 1 + m) + (T(1) - th) * SI(p, 4 + c, 1 + m);
-                        dguc[m] = th * SI(p, 7 + c, 1 + m);
-                        dgcol[m] = th * SI(p, 7 + m, 1 + c);
-                    }
-                    const T atc = (SI(p, c, 0) - SI(p, 4 + c, 0)) * idt;
-                    const T datc = SI(p, 7 + c, 0) * idt;
-                    const T convc = ut[0] * guc[0] + ut[1] * guc[1] + ut[2] * guc[2];
-                    const T dconvc = dut[0] * guc[0] + dut[1] * guc[1] + dut[2] * guc[2] +
-                                     ut[0] * dguc[0] + ut[1] * dguc[1] + ut[2] * dguc[2];
-                    const T upc = -tauM * (rho * (atc + convc) + SI(p, 3, 1 + c));
-                    const T dupc = -tauM * (rho * (datc + dconvc) + SI(p, 10, 1 + c));
-                    T sv = T(0), dsv = T(0);
-                    for (int m = 0; m < 3; ++m) {
-                        sv += up[m] * guc[m];
-                        dsv += dup[m] * guc[m] + up[m] * dguc[m];
-                    }
-                    const T dpr = SI(p, 10, 0);
-                    q[QRC + 4 * c] = W * (rho * datc + rho * dconvc + dsv);
-                    for (int k = 0; k < 3; ++k)
-                        q[QRC + 4 * c + 1 + k] =
-                            W * (mu * (dguc[k] + dgcol[k]) - (k == c ? dpr + dpp : T(0)) -
-                                 dut[k] * upc - ut[k] * dupc - (dup[k] * upc + up[k] * dupc) * irho +
-                                 tb * (dup[k] * sv + up[k] * dsv));
-                } else {
-                    q[QRC + 12] = W * ddiv;
-                    for (int k = 0; k < 3; ++k) q[QRC + 13 + k] = -W * dup[k] * irho;
-                }
-            }
-        } else {
+        {
             const int p = lane >> 3, r = lane & 7;
             if (p < np && r < 4) {
                 T ut[3], gu[3][3], up[3];
@@ -443,7 +315,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
         // (p, r): r < 3 the matrix rows c = r, 3 <= r < 6 the vector
         // components c = r - 3. The round trip through LDS bounds the registers
         // the point phase holds.
-        if (MAT) {
+        {
             __syncthreads();
             const int p = lane >> 3, r = lane & 7;
             if (p < np && r < 6) {
@@ -473,7 +345,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
             }
         }
         __syncthreads();
-        if (MAT) {
+        {
             // ---- phases 4 and 5 over batches of PD points
             for (int pb = 0; pb < np; pb += PD) {
             const int nd = min(PD, np - pb);
@@ -524,34 +396,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
             __syncthreads();
             // ---- phase 5: stage 1 (VALU) and stage 2 (MFMA)
             const int col = lane & 15, bb = col >> 2, jc = col & 3;
-            if (MODE == 0) {
-                // Both stages on 4x4x4 MFMA. Lane l carries, in every operand,
-                // index l / 16 of the contraction, block (l / 4) % 4 = trial
-                // component j and row / column l % 4. Stage 1, per (i, b half bh):
-                // E^{ij}[k][4 bh + n] = sum_l D^{ij}[k][l] B[l][4 bh + n], with A =
-                // D^{ij} read transposed from LDS and B = basis columns 4 bh + n;
-                // its output lands in exactly the layout of stage 2's B operand
-                // (k = l / 16, j, n = l % 4). Stage 2: K^{ij}[4 ah + m][4 bh + n] +=
-                // sum_k B[k][4 ah + m] E^{ij}[k][4 bh + n]. The basis values A0 / A1
-                // (rows 0-3 / 4-7) serve as stage 1's B and stage 2's A alike.
-                const int k = lane >> 4, j4 = (lane >> 2) & 3, n4 = lane & 3;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    if (p >= nd) break;
-                    const double A0 = (double)SB(pb + p, k, n4), A1 = (double)SB(pb + p, k, 4 + n4);
-                    const double Ar = j4 == 0 ? A0 : (j4 == 1 ? A1 : 0.0);
-                    const double rc = (double)sQ[pb + p][QRC + 4 * n4 + k];
-                    accr = __builtin_amdgcn_mfma_f64_4x4x4f64(Ar, rc, accr, 0, 0, 0);
-                    for (int i = 0; i < 4; ++i) {
-                        const double Dt = (double)SD(p, i, j4, n4, k);  // D^{ij}[n4][k]
-                        for (int bh = 0; bh < 2; ++bh) {
-                            const double E = __builtin_amdgcn_mfma_f64_4x4x4f64(Dt, bh ? A1 : A0, 0.0, 0, 0, 0);
-                            acc4[i][0][bh] = __builtin_amdgcn_mfma_f64_4x4x4f64(A0, E, acc4[i][0][bh], 0, 0, 0);
-                            acc4[i][1][bh] = __builtin_amdgcn_mfma_f64_4x4x4f64(A1, E, acc4[i][1][bh], 0, 0, 0);
-                        }
-                    }
-                }
-            } else {
+            {
                 // k-step of 32 = 8 points x 4 derivative rows; lane group g holds points 2g, 2g+1
                 const int g = lane >> 4, row = lane & 15;
                 const int ar = row & 7;
@@ -677,7 +522,7 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
             }  // batches of PD points
         }
         // residual: lanes < 32, (a = lane & 7, i = lane >> 3)
-        if (!RES_MFMA && lane < 32) {
+        if (lane < 32) {
             const int av = lane & 7, i = lane >> 3;
             for (int p = 0; p < np; ++p)
                 R += SB(p, 0, av) * sQ[p][QRC + 4 * i] + SB(p, 1, av) * sQ[p][QRC + 4 * i + 1] +
@@ -691,26 +536,13 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
     // (block (a, b) of master slots, entry 4 i + j), stored from the
     // accumulators; the CSR is summed from these records by the gather kernel
     // (no atomics, fixed summation order)
-    if (MAT && a.vals) {
+    if (a.vals) {
         // atomic scatter: no record; each entry is added into its CSR place
         // (the summation order is the hardware's)
         T *vals = (T *)a.vals;
         const int32_t *mst = a.masters + 8 * (int64_t)e;
         const uint16_t *kk = a.el_kk + 64 * (int64_t)e;
-        if (MODE == 0) {
-            const int m4 = lane >> 4, j4 = (lane >> 2) & 3, n4 = lane & 3;
-            for (int ah = 0; ah < 2; ++ah) {
-                const int av = 4 * ah + m4, ma = mst[av];
-                if (ma < 0) continue;
-                const int64_t r0 = a.nrow_ptr[ma], deg = a.nrow_ptr[ma + 1] - r0;
-                for (int bh = 0; bh < 2; ++bh) {
-                    const int b = 4 * bh + n4;
-                    if (mst[b] < 0) continue;
-                    T *dst = vals + 16 * r0 + 4 * (int64_t)kk[8 * av + b] + j4;
-                    for (int i = 0; i < 4; ++i) atomicAdd(dst + 4 * i * deg, (T)acc4[i][ah][bh]);
-                }
-            }
-        } else {
+        {
             const int col = lane & 15, bb = col >> 2, jc = col & 3;
             const float unscale = (MODE == 2 && s16 != INT_MAX) ? ldexpf(1.0f, -s16) : 1.0f;
             // rows av = 4 (lane / 16) + r of the lanes < 32, columns b = 4 h + bb
@@ -736,16 +568,10 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
                 }
             }
         }
-    } else if (MAT) {
+    } else {
         const int col = lane & 15, bb = col >> 2, jc = col & 3;
         T *dst = (T *)a.em + (a.slot0 + item) * 1024;
-        if (MODE == 0) {
-            const int m4 = lane >> 4, j4 = (lane >> 2) & 3, n4 = lane & 3;
-            for (int i = 0; i < 4; ++i)
-                for (int ah = 0; ah < 2; ++ah)
-                    for (int bh = 0; bh < 2; ++bh)
-                        dst[((4 * ah + m4) * 8 + 4 * bh + n4) * 16 + 4 * i + j4] = (T)acc4[i][ah][bh];
-        } else {
+        {
             // rows 8..15 carry the second split term: fold them onto rows 0..7
             const float unscale = (MODE == 2 && s16 != INT_MAX) ? ldexpf(1.0f, -s16) : 1.0f;
             for (int t = 0; t < 8; ++t) {
@@ -763,43 +589,339 @@ __device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item,
     }
     // residual record of the work item (entry 4 a + i); the residual is summed
     // from the records by node, in a fixed order
-    if (RES_MFMA) {
-        const int blk = (lane >> 2) & 3;
-        if (blk < 2 && a.rrec) {
-            const int av = 4 * blk + (lane >> 4), i = lane & 3;
-            a.rrec[(a.slot0 + item) * 32 + 4 * av + i] = accr;
-        }
-    } else if (lane < 32 && a.rrec) {
+    if (lane < 32 && a.rrec) {
         const int av = lane & 7, i = lane >> 3;
         a.rrec[(a.slot0 + item) * 32 + 4 * av + i] = (double)R;
     }
 }
 
-// waves per SIMD the register allocation aims for: the LDS of one item
-// allows 8 (FP64) or 11 (mixed) one-wave workgroups per CU (4 SIMDs)
-#ifndef VMS_WPE64
-#define VMS_WPE64 2
-#endif
-#ifndef VMS_WPEMX
-#define VMS_WPEMX 3
-#endif
-#define VMS_ASM_BOUNDS(MODE) \
-    __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((MODE) == 0 ? VMS_WPE64 : VMS_WPEMX, 8)))
+// ---------------------------------------------------------------------------
+// FP64 element matrices
+// ---------------------------------------------------------------------------
+//
+// Both contraction stages run on v_mfma_f64_4x4x4 (four 4x4 blocks per
+// instruction, block = test component i). Stage 1 forms, per trial component
+// j and half bh of the trial functions, F^{ij}[r][4 bh + n] = sum_c
+// D^{ij}[r][c] B[c][4 bh + n]; its output registers have the layout of stage
+// 2's second operand, and stage 2 adds B^T F into the 4x4 blocks of the 8x8
+// component-pair block.
+//
+// The D blocks never exist as blocks: lane (c, i, r) of stage 1's first operand
+// needs one entry D^{ij}[r][c] per j, and evaluates it from the point's table
+// (PQ below) with lane constants in place of the case distinctions. With
+// T1 = (rho, Y), T2 = (-tau rho, X), T3 = (1, taubar u') over the rows r,
+// alpha = (1/dt, theta u) over the columns c, k = r - 1, l = c - 1,
+// c_3 = tau_M and H = (grad u)^2, all times the weight:
+//   D^{ij}[r][c] = g_ij (alpha T2 + z0 T1) + d_ij (alpha T1 + theta u'_l T3 + mu theta d_kl)
+//                + d_kj (alpha c_i - z0 u'_i + mu theta d_il) + z0 (T2 H_ij + c_i g_kj)
+//                + d_lj (rho tau_C theta d_ki + theta d_i3 d_r0),     j < 3,
+//   D^{i3}[r][c] = (T2 g_il + d_il T1 + d_kl c_i) / rho (c > 0), -d_ki (c = 0),
+// z0 = theta on c = 0 and 0 elsewhere, terms with k dropped on r = 0 and terms
+// with l on c = 0. This is dblock_mv / dblock_simple of vms_point.h written per
+// entry.
+//
+// What bounds it: issue. A probe of independent chains (four waves per SIMD)
+// takes 18 cycles per v_mfma_f64_4x4x4 and 5.4 per v_fma_f64 at a nominal 2.4
+// GHz, and a loop of both takes their sum: the matrix instruction does not run
+// beside FP64 or FP32 VALU work, so every instruction counts. Per point 25
+// MFMA, about 30 FP64 operations and 20 LDS reads for the D entries; with the
+// blocks evaluated in two divergent passes, written to LDS (17.2 KB per
+// workgroup, 2.25 waves per SIMD) and read back, the OUT elements of the
+// 194k-octant sphere took 0.625 ms and its sub-cell items 2.19 ms; now 0.504 and
+// 1.89 ms with 9.8 KB.
+#define PQ_T12 0   // (T1, T2)[r], pairs
+#define PQ_AUP 8   // (alpha, theta u')[c], pairs
+#define PQ_CUP 16  // (c, u')[i], pairs; i = 3: (tau_M, 0)
+#define PQ_T3 24   // T3[r]
+#define PQ_G 28    // grad u rows i, 3 entries each; row 3 zero
+#define PQ_H 40    // (grad u)^2 rows i
+#define PQ_E1 49   // 0 0 rho tau_C theta 0 0: the unit row l starts at 2 - l
+#define PQ_E2 54   // 0 0 theta 0 0
+#define PQ_W 59
+#define PQ_RC 60   // 16 residual coefficients r^i[k]
+#define PQ_N 77
+
+// Fields at the master slots are combined as they are loaded: rows 0-2
+// u_theta, 3 p, 4-6 the rate (u - u_prev) / dt, of which only the value is
+// interpolated.
+struct Smem64 {
+    double sU[7 * LU];
+    double sC[64];
+    double sB[8 * LB];
+    double sI[8 * 21];  // per point: u_theta and gradient (4 each), p and gradient, rate (3)
+    double sQ[8 * PQ_N];
+};
+
+template <bool SUB>
+__device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item, Smem64 &sm, const ItemPre *pre) {
+    const int lane = threadIdx.x;
+    __syncthreads();  // the previous item of this workgroup is done with the LDS
+    const int e = pre ? pre->e : a.items[item];
+    const bool hang = (pre ? pre->hang : a.has_hang[e]) != 0;
+    const int lev = pre ? pre->level : (int)a.level[e];
+    const double h = ldexp(a.root_len, -lev);
+    const double two_over_h = ldexp(a.two_over_root, lev);
+    const double rho = a.rho, mu = a.mu, th = a.theta, idt = a.idt, irho = a.irho;
+    {
+        uint32_t code;
+        double fv;
+        if (pre) {
+            code = pre->code;
+            fv = pre->fv;
+        } else {
+            const int bit = 2 * lane;
+            code = (a.ccode[4 * (int64_t)e + (bit >> 5)] >> (bit & 31)) & 3u;
+            const int m = a.masters[8 * (int64_t)e + (lane & 7)];
+            fv = (lane < 56 && m >= 0) ? field_in(a, lane >> 3)[m] : 0.0;
+        }
+        sm.sC[lane] = code == 3u ? 1.0 : (code == 2u ? 0.5 : (code == 1u ? 0.25 : 0.0));
+        const double other = __shfl_xor(fv, 32, 64);  // fields f and f + 4
+        if (lane < 24) fv = th * fv + (1.0 - th) * other;
+        else if (lane >= 32) fv = (other - fv) * idt;
+        if (lane < 56) sm.sU[(lane >> 3) * LU + (lane & 7)] = fv;
+    }
+    const int npts = SUB ? a.pt_cnt[item] : 8;
+    // G = (2/h)^2 I: u.G.u = gG |u|^2; tau_M^-2 = c_t/dt^2 + gG |u|^2 + c_i nu^2 G:G;
+    // tau_C = 1/(tau_M tr G) = (h^2/12)/tau_M
+    const double gG = two_over_h * two_over_h;
+    const double tau0 = a.tau_a + a.tau_b * gG * gG;
+    const double h2_12 = h * h * (1.0 / 12.0);
+
+    // lane constants of the D entries
+    const int c4 = lane >> 4, i4 = (lane >> 2) & 3, r4 = lane & 3, kr = r4 - 1, lc = c4 - 1;
+    const double z0 = c4 == 0 ? th : 0.0, n0 = c4 == 0 ? 0.0 : 1.0;
+    double dk[3], di[3];
+    for (int j = 0; j < 3; ++j) {
+        dk[j] = kr == j ? 1.0 : 0.0;
+        di[j] = i4 == j ? 1.0 : 0.0;
+    }
+    const double kil = (c4 > 0 && i4 == lc) ? mu * th : 0.0;
+    const double kkl = (c4 > 0 && kr == lc) ? mu * th : 0.0;
+    const double mc = c4 > 0 ? irho : 0.0;
+    const double m1 = (c4 > 0 && i4 == lc && r4 > 0) ? irho : 0.0, m2 = (c4 > 0 && kr == lc) ? irho : 0.0;
+    const double m3 = (c4 == 0 && r4 > 0 && kr == i4) ? -1.0 : 0.0;
+    const int x_at = c4 == 0 ? (i4 < 3 ? PQ_H + 3 * i4 : PQ_G + 9)
+                             : (r4 > 0 && kr == i4 ? PQ_E1 + 2 - lc
+                                                   : (i4 == 3 && r4 == 0 ? PQ_E2 + 2 - lc : PQ_G + 9));
+    const int gi_at = PQ_G + 3 * i4, gk_at = PQ_G + (r4 > 0 ? 3 * kr : 9);
+    const int gl_at = gi_at + (c4 > 0 ? lc : 0);
+
+    // K^{ij}[4 ah + m][4 bh + n] in lane (m = lane / 16, i, n = lane % 4)
+    double acc[2][2][4];
+    for (int t = 0; t < 16; ++t) acc[t >> 3][(t >> 2) & 1][t & 3] = 0.0;
+    // the residual is one more MFMA whose blocks 0 and 1 are the two halves of
+    // the rows a (columns i carry r^i[k]): lane l holds R[4 ((l / 4) % 4) + l / 16][l % 4]
+    double accr = 0.0;
+    // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
+    const int p8 = lane >> 3, s8 = lane & 7;
+    const int64_t eoff = SUB ? a.pt_off[item] : 0;
+    uint32_t en_cur = (SUB && p8 < npts) ? a.entries[eoff + p8] : 0u;
+    __syncthreads();
+
+    for (int base = 0; base < npts; base += 8) {
+        const int np = min(8, npts - base);
+        const int pn = base + 8 + p8;
+        const uint32_t en_next = (SUB && pn < npts) ? a.entries[eoff + pn] : 0u;
+        // ---- phase 1: constrained basis at the chunk's points (lane = (p, s));
+        // points beyond the item's last have weight 0
+        double w;
+        {
+            double xi[3], b[4] = {0.0, 0.0, 0.0, 0.0};
+            point_xw<SUB>(a, en_cur, SUB ? 0 : p8, h, xi, w);
+            if (SUB && p8 >= np) w = 0.0;
+            const double hg = 0.5 * two_over_h;
+            // vertex v of the constrained slot s: v = s without hanging
+            // corners, else every v with C[v][s] != 0
+            const int v0 = hang ? 0 : s8, v1 = hang ? 8 : s8 + 1;
+#pragma unroll 1
+            for (int v = v0; v < v1; ++v) {
+                const double c = hang ? sm.sC[v * 8 + s8] : 1.0;
+                if (c == 0.0) continue;
+                double f[3], g[3];
+                for (int k = 0; k < 3; ++k) {
+                    const bool up = (v >> k) & 1;
+                    f[k] = 0.5 * (up ? 1.0 + xi[k] : 1.0 - xi[k]);
+                    g[k] = up ? hg : -hg;
+                }
+                b[0] += c * (f[0] * f[1] * f[2]);
+                b[1] += c * (g[0] * f[1] * f[2]);
+                b[2] += c * (f[0] * g[1] * f[2]);
+                b[3] += c * (f[0] * f[1] * g[2]);
+            }
+            for (int k = 0; k < 4; ++k) sm.sB[p8 * LB + k * 8 + s8] = b[k];
+        }
+        __syncthreads();
+        // ---- phase 2: interpolation of the nodal fields (lane = (p, field))
+        if (s8 < 7) {
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int s = 0; s < 8; ++s) {
+                const double u = sm.sU[s8 * LU + s];
+                for (int k = 0; k < 4; ++k) v[k] += sm.sB[p8 * LB + k * 8 + s] * u;
+            }
+            double *I = sm.sI + p8 * 21;
+            if (s8 < 4) {
+                for (int k = 0; k < 4; ++k) I[4 * s8 + k] = v[k];
+            } else {
+                I[12 + s8] = v[0];
+            }
+        }
+        __syncthreads();
+        // ---- phase 3: the point's table. Lanes r < 3 of point p take row / component
+        // r of it; with every component index rotated by r their own row is index
+        // 0, so that no register array is indexed by the lane. Lane r = 3 writes
+        // the scalars and the continuity row.
+        if (s8 < 4) {
+            const double *I = sm.sI + p8 * 21;
+            const int o[3] = {s8 < 3 ? s8 : 0, s8 < 3 ? (s8 + 1 < 3 ? s8 + 1 : 0) : 1,
+                              s8 < 3 ? (s8 + 2 < 3 ? s8 + 2 : s8 - 1) : 2};
+            double ut[3], gu[3][3], up[3], acl[3];
+            for (int c = 0; c < 3; ++c) {
+                ut[c] = I[4 * o[c]];
+                for (int m = 0; m < 3; ++m) gu[c][m] = I[4 * o[c] + 1 + o[m]];
+            }
+            const double s0 = tau0 + gG * (ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2]);
+            const double tauM = rsq<double>(s0);
+            const double tauC = h2_12 * s0 * tauM;
+            for (int c = 0; c < 3; ++c) {
+                acl[c] = I[16 + o[c]] + ut[0] * gu[c][0] + ut[1] * gu[c][1] + ut[2] * gu[c][2];
+                up[c] = -tauM * (rho * acl[c] + I[13 + o[c]]);
+            }
+            const double div = gu[0][0] + gu[1][1] + gu[2][2];
+            const double pp = -rho * tauC * div;
+            const double upg = gG * (up[0] * up[0] + up[1] * up[1] + up[2] * up[2]);
+            const double tb = upg > 0.0 ? rsq<double>(upg) : 0.0;
+            double *q = sm.sQ + p8 * PQ_N;
+            if (s8 < 3) {
+                const int c = s8;
+                const double sv = up[0] * gu[0][0] + up[1] * gu[0][1] + up[2] * gu[0][2];
+                const double Wt = w * tauM, tbr = tb * rho;
+                q[PQ_T12 + 2 * (c + 1)] = Wt * (rho * ut[0] + up[0]);
+                q[PQ_T12 + 2 * (c + 1) + 1] = -Wt * tbr * up[0];
+                q[PQ_AUP + 2 * (c + 1)] = th * ut[0];
+                q[PQ_AUP + 2 * (c + 1) + 1] = th * up[0];
+                q[PQ_CUP + 2 * c] = Wt * (up[0] - tbr * sv);
+                q[PQ_CUP + 2 * c + 1] = w * up[0];
+                q[PQ_T3 + 1 + c] = w * tb * up[0];
+                for (int m = 0; m < 3; ++m) {
+                    q[PQ_G + 3 * c + o[m]] = gu[0][m];
+                    q[PQ_H + 3 * c + o[m]] = gu[0][0] * gu[0][m] + gu[0][1] * gu[1][m] + gu[0][2] * gu[2][m];
+                    const double t = mu * (gu[0][m] + gu[m][0]) - ut[m] * up[0] - up[m] * up[0] * irho + tb * up[m] * sv;
+                    q[PQ_RC + 4 * c + 1 + o[m]] = w * (m == 0 ? t - (I[12] + pp) : t);
+                }
+                q[PQ_RC + 4 * c] = w * (rho * acl[0] + sv);
+                q[PQ_G + 9 + c] = 0.0;
+            } else {
+                q[PQ_T12] = w * rho;
+                q[PQ_T12 + 1] = -w * tauM * rho;
+                q[PQ_AUP] = idt;
+                q[PQ_AUP + 1] = 0.0;
+                q[PQ_CUP + 6] = w * tauM;
+                q[PQ_CUP + 7] = 0.0;
+                q[PQ_T3] = w;
+                q[PQ_E1] = q[PQ_E1 + 1] = q[PQ_E1 + 3] = q[PQ_E1 + 4] = 0.0;
+                q[PQ_E2] = q[PQ_E2 + 1] = q[PQ_E2 + 3] = q[PQ_E2 + 4] = 0.0;
+                q[PQ_E1 + 2] = w * rho * tauC * th;
+                q[PQ_E2 + 2] = w * th;
+                q[PQ_W] = w;
+                q[PQ_RC + 12] = w * div;
+                for (int k = 0; k < 3; ++k) q[PQ_RC + 13 + k] = -w * up[k] * irho;
+            }
+        }
+        __syncthreads();
+        // ---- phase 4: D entries, stage 1, stage 2
+        const int n2 = SUB ? (np + 1) & ~1 : 8;
+#pragma unroll 1
+        for (int p = 0; p < n2; ++p) {
+            const double *q = sm.sQ + p * PQ_N;
+            const double *B = sm.sB + p * LB + c4 * 8 + r4;
+            const double A0 = B[0], A1 = B[4];
+            const double T1 = q[PQ_T12 + 2 * r4], T2 = q[PQ_T12 + 2 * r4 + 1];
+            const double al = q[PQ_AUP + 2 * c4], ul = q[PQ_AUP + 2 * c4 + 1];
+            const double ci = q[PQ_CUP + 2 * i4], ui = q[PQ_CUP + 2 * i4 + 1];
+            const double T3 = q[PQ_T3 + r4], W = q[PQ_W], gl = q[gl_at];
+            const double Ar = i4 == 0 ? A0 : (i4 == 1 ? A1 : 0.0);
+            accr = __builtin_amdgcn_mfma_f64_4x4x4f64(Ar, q[PQ_RC + 4 * r4 + c4], accr, 0, 0, 0);
+            const double a1 = al * T2 + z0 * T1;
+            const double bk = al * ci - z0 * ui + kil * W;
+            const double a5 = al * T1 + ul * T3 + kkl * W;
+            const double y1 = z0 * T2 + n0, y2 = z0 * ci;
+            double D[4];
+            for (int j = 0; j < 3; ++j)
+                D[j] = a1 * q[gi_at + j] + y1 * q[x_at + j] + y2 * q[gk_at + j] + dk[j] * bk + di[j] * a5;
+            D[3] = mc * T2 * gl + m1 * T1 + m2 * ci + m3 * W;
+            double F[4][2];
+            for (int j = 0; j < 4; ++j)
+                for (int bh = 0; bh < 2; ++bh)
+                    F[j][bh] = __builtin_amdgcn_mfma_f64_4x4x4f64(D[j], bh ? A1 : A0, 0.0, 0, 0, 0);
+            for (int j = 0; j < 4; ++j)
+                for (int bh = 0; bh < 2; ++bh) {
+                    acc[0][bh][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(A0, F[j][bh], acc[0][bh][j], 0, 0, 0);
+                    acc[1][bh][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(A1, F[j][bh], acc[1][bh][j], 0, 0, 0);
+                }
+        }
+        en_cur = en_next;
+        __syncthreads();
+    }
+
+    if (a.vals) {
+        // atomic scatter: no record; each entry is added into its CSR place
+        // (the summation order is the hardware's)
+        double *vals = (double *)a.vals;
+        const int32_t *mst = a.masters + 8 * (int64_t)e;
+        const uint16_t *kk = a.el_kk + 64 * (int64_t)e;
+        for (int ah = 0; ah < 2; ++ah) {
+            const int av = 4 * ah + c4, ma = mst[av];
+            if (ma < 0) continue;
+            const int64_t r0 = a.nrow_ptr[ma], deg = a.nrow_ptr[ma + 1] - r0;
+            for (int bh = 0; bh < 2; ++bh) {
+                const int b = 4 * bh + r4;
+                if (mst[b] < 0) continue;
+                double *dst = vals + 16 * r0 + 4 * (int64_t)kk[8 * av + b] + 4 * i4 * deg;
+                for (int j = 0; j < 4; ++j) atomicAdd(dst + j, acc[ah][bh][j]);
+            }
+        }
+    } else {
+        // record of the work item, block-major (block (a, b) of master slots,
+        // entry 4 i + j): a lane's four entries j are 32 contiguous bytes, 16
+        // lanes write 512
+        double *dst = (double *)a.em + (a.slot0 + item) * 1024;
+        for (int ah = 0; ah < 2; ++ah)
+            for (int bh = 0; bh < 2; ++bh) {
+                const double *v = acc[ah][bh];
+                *(v4d *)(dst + ((4 * ah + c4) * 8 + 4 * bh + r4) * 16 + 4 * i4) = v4d{v[0], v[1], v[2], v[3]};
+            }
+    }
+    // residual record of the work item (entry 4 a + i)
+    if (i4 < 2 && a.rrec) a.rrec[(a.slot0 + item) * 32 + 4 * (4 * i4 + c4) + r4] = accr;
+}
+
+// Waves per SIMD the register allocation aims for. The FP64 matrix kernels fit
+// three (OUT elements: 160 VGPRs; at four they spill, 3.00 -> 3.60 ms per step
+// on the 194k-octant sphere). The FP64 sub-cell items stay at two: they run
+// beside the HBM-bound gather, which needs the other registers for its own
+// waves (two-box step of 1.6M octants 12.30 ms at three, 11.75 ms at two; the
+// sphere, where the items outlast the gather, 3.01 against 3.03 ms).
+#define VMS_ASM_BOUNDS(MODE, SUB) \
+    __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((MODE) == 0 && (SUB) ? 2 : 3, 8)))
 
 // OUT elements (SUB = false) two per workgroup: the second element's data
 // and fields load while the first is assembled
-template <typename T, int MODE, bool SUB, bool MAT>
-__global__ VMS_ASM_BOUNDS(MODE) void k_asm2(AsmArgs a) {
-    __shared__ Smem<T, MODE == 0 ? 4 : 8, MAT, 7> sm;
+template <typename T, int MODE, bool SUB>
+__global__ VMS_ASM_BOUNDS(MODE, SUB) void k_asm2(AsmArgs a) {
+    __shared__ std::conditional_t<MODE == 0, Smem64, Smem<T>> sm;
+    auto item = [&](int64_t i, const ItemPre *pre) {
+        if constexpr (MODE == 0) asm_item64<SUB>(a, i, sm, pre);
+        else asm_item<T, MODE, SUB>(a, i, sm, pre);
+    };
     if constexpr (SUB) {
-        asm_item<T, MODE, SUB, MAT, MODE == 0 ? 4 : 8>(a, blockIdx.x, sm);
+        item(blockIdx.x, nullptr);
     } else {
-        const int64_t i0 = 2 * (int64_t)blockIdx.x, i1 = i0 + 1;
-        const bool has1 = i1 < a.n_items;
+        const int64_t i0 = (int64_t)blockIdx.x << a.pair, i1 = i0 + 1;
+        const bool has1 = a.pair && i1 < a.n_items;
         ItemPre P0, P1;
         load_pre2(a, i0, i1, has1, P0, P1);
-        asm_item<T, MODE, SUB, MAT, MODE == 0 ? 4 : 8>(a, i0, sm, nullptr, &P0);
-        if (has1) asm_item<T, MODE, SUB, MAT, MODE == 0 ? 4 : 8>(a, i1, sm, nullptr, &P1);
+        item(i0, &P0);
+        if (has1) item(i1, &P1);
     }
 }
 
@@ -808,11 +930,10 @@ __global__ VMS_ASM_BOUNDS(MODE) void k_asm2(AsmArgs a) {
 // (heaviest first); a unit is a run of OUT elements or of sub-cell work items
 // of one tree. One launch for all units.
 template <typename T, int MODE>
-__global__ VMS_ASM_BOUNDS(MODE) void k_asm_batch(const AsmArgs *std_args, const AsmArgs *sub_args,
+__global__ VMS_ASM_BOUNDS(MODE, true) void k_asm_batch(const AsmArgs *std_args, const AsmArgs *sub_args,
                                                  const BatchUnit *units, int64_t n_units,
                                                  unsigned long long *counter) {
-    constexpr int PTS = MODE == 0 ? 4 : 8;
-    __shared__ Smem<T, PTS, true, 7> sm;
+    __shared__ std::conditional_t<MODE == 0, Smem64, Smem<T>> sm;
     __shared__ int64_t su;
     __shared__ AsmArgs sa;  // the unit's tree, read from LDS where used
     for (;;) {
@@ -824,10 +945,16 @@ __global__ VMS_ASM_BOUNDS(MODE) void k_asm_batch(const AsmArgs *std_args, const 
         const BatchUnit U = units[u];
         if (threadIdx.x == 0) sa = U.sub ? sub_args[U.tree] : std_args[U.tree];
         __syncthreads();
-        if (U.sub) {
-            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, true, true, PTS>(sa, U.first + k, sm);
+        if constexpr (MODE == 0) {
+            if (U.sub) {
+                for (int k = 0; k < U.count; ++k) asm_item64<true>(sa, U.first + k, sm, nullptr);
+            } else {
+                for (int k = 0; k < U.count; ++k) asm_item64<false>(sa, U.first + k, sm, nullptr);
+            }
+        } else if (U.sub) {
+            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, true>(sa, U.first + k, sm);
         } else {
-            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, false, true, PTS>(sa, U.first + k, sm);
+            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, false>(sa, U.first + k, sm);
         }
     }
 }
@@ -1043,34 +1170,43 @@ size_t lds_for_cap(const void *kernel, int wg_per_cu) {
 }
 
 int sub_items_per_cu(int precision) {
-    const void *k = precision == 0 ? (const void *)&k_asm2<double, 0, true, true>
-                    : precision == 1 ? (const void *)&k_asm2<float, 1, true, true>
-                                     : (const void *)&k_asm2<float, 2, true, true>;
+    const void *k = precision == 0 ? (const void *)&k_asm2<double, 0, true>
+                    : precision == 1 ? (const void *)&k_asm2<float, 1, true>
+                                     : (const void *)&k_asm2<float, 2, true>;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 64, 0) != hipSuccess) return 0;
     return n;
 }
 
-void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, int wg_per_cu) {
-    if (a.n_items <= 0) return;
-    dim3 grid((unsigned)(sub ? a.n_items : (a.n_items + 1) / 2)), block(64);
-    if (sub)
-        hipLaunchKernelGGL((k_asm2<double, 0, true, true>), grid, block,
-                           lds_for_cap((const void *)&k_asm2<double, 0, true, true>, wg_per_cu), s, a);
-    else
-        hipLaunchKernelGGL((k_asm2<double, 0, false, true>), grid, block, 0, s, a);
+// OUT elements go two per workgroup (the second one's loads in flight while the
+// first is assembled) only where one each would give more workgroups than the
+// GPU holds at once; below that two in a row only lengthen the one round of
+// workgroups
+static dim3 item_grid(AsmArgs &a, bool sub) {
+    a.pair = !sub && a.n_items > 256 * 12;
+    return dim3((unsigned)(a.pair ? (a.n_items + 1) / 2 : a.n_items));
 }
 
-void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, int fp16, int wg_per_cu) {
+void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu) {
     if (a.n_items <= 0) return;
-    dim3 grid((unsigned)(sub ? a.n_items : (a.n_items + 1) / 2)), block(64);
+    const dim3 grid = item_grid(a, sub), block(64);
+    if (sub)
+        hipLaunchKernelGGL((k_asm2<double, 0, true>), grid, block,
+                           lds_for_cap((const void *)&k_asm2<double, 0, true>, wg_per_cu), s, a);
+    else
+        hipLaunchKernelGGL((k_asm2<double, 0, false>), grid, block, 0, s, a);
+}
+
+void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu) {
+    if (a.n_items <= 0) return;
+    const dim3 grid = item_grid(a, sub), block(64);
 #define VMS_L(MODE)                                                                             \
     do {                                                                                        \
         if (sub)                                                                                \
-            hipLaunchKernelGGL((k_asm2<float, MODE, true, true>), grid, block,                  \
-                               lds_for_cap((const void *)&k_asm2<float, MODE, true, true>, wg_per_cu), s, a); \
+            hipLaunchKernelGGL((k_asm2<float, MODE, true>), grid, block,                        \
+                               lds_for_cap((const void *)&k_asm2<float, MODE, true>, wg_per_cu), s, a); \
         else                                                                                    \
-            hipLaunchKernelGGL((k_asm2<float, MODE, false, true>), grid, block, 0, s, a);       \
+            hipLaunchKernelGGL((k_asm2<float, MODE, false>), grid, block, 0, s, a);             \
     } while (0)
     if (fp16) VMS_L(2);
     else VMS_L(1);

@@ -119,6 +119,7 @@ struct AsmArgs {
     const uint8_t *level;     // [E]
     // work list
     int64_t n_items;
+    int32_t pair;             // OUT elements two per workgroup (set by the launch)
     const int32_t *items;     // element ids
     const int64_t *pt_off;    // SUB: first entry of the item's points
     const int32_t *pt_cnt;    // SUB: number of points
@@ -162,7 +163,7 @@ inline void set_params(AsmArgs &a, double rho, double mu, double dt, double thet
 // wg_per_cu > 0 (sub-cell items only): dynamic LDS so that at most that many
 // workgroups share a CU, leaving the rest of its waves to another stream's
 // kernel
-void launch_assemble_f64(hipStream_t s, const AsmArgs &a, bool sub, int wg_per_cu = 0);
+void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu = 0);
 
 // one unit of the persistent batched assembly: items [first, first + count) of
 // tree `tree`'s OUT-element list (sub = 0) or sub-cell work-item list (sub = 1)
@@ -178,7 +179,7 @@ struct BatchUnit {
 void launch_assemble_batch(hipStream_t s, int precision, const AsmArgs *std_args,
                            const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
                            unsigned long long *counter, int n_groups);
-void launch_assemble_mixed(hipStream_t s, const AsmArgs &a, bool sub, int fp16, int wg_per_cu = 0);
+void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu = 0);
 // resident workgroups per CU of the sub-cell item kernel of a precision form
 // (0 FP64, 1 BF16x3, 2 FP16x2; with the matrix), from its registers and LDS
 int sub_items_per_cu(int precision);
