@@ -2353,7 +2353,7 @@ void batch_enqueue(vms_batch *b, bool timed) {
     if (timed) (void)hipEventRecord(b->ev[0], b->stream);
     if (timed) (void)hipEventRecord(b->ev[1], b->stream);
     vmsk::launch_assemble_batch(b->stream, b->precision, b->d_std, b->d_sub, b->d_units, b->n_units,
-                                b->d_counter, b->n_cu * b->groups_per_cu);
+                                b->d_counter, b->n_cu * b->groups_per_cu, b->n_cu);
     if (timed) (void)hipEventRecord(b->ev[2], b->stream);
     vmsk::launch_gather_batch(b->stream, b->precision, b->d_tabs, b->d_blk_prefix, b->tot_blocks,
                               b->d_node_prefix, b->tot_nodes, (int)b->ctx.size());

@@ -21,17 +21,13 @@
 // Stage 2 is a GEMM over the 8 basis rows a, the contraction over (point,
 // derivative) and the 128 columns (b, j, i).
 //
-// Precision forms. FP64 runs both stages on v_mfma_f64_4x4x4 (four 4x4
-// blocks per instruction, block = trial component j): stage 1 produces, per
-// (i, b half), the 4x4 blocks F^{ij}[k][b] directly in the register layout of
-// stage 2's second operand, and stage 2 adds them into the four 4x4 blocks of
-// each 8x8 component-pair block (no idle rows, one point per k-step).
+// Precision forms. FP64 runs both stages on v_mfma_f64_4x4x4 (asm_item64).
 // MIXED_BF16 splits both stage-2 operands into three bf16 terms and
 // MIXED_FP16 into two fp16 terms (with power-of-two scaling), accumulating in
 // FP32 with v_mfma_f32_16x16x32 (eight points per k-step; rows a in 16-row
 // tiles with the second split term in rows 8-15); stage 1 and everything
 // before the contraction run in FP32 on the VALU and the result is written
-// as FP32.
+// as FP32 (asm_item32).
 //
 // One 64-lane workgroup per element, points in chunks of 8.
 #include "item_dev.h"
@@ -75,34 +71,7 @@ __device__ inline void split2hx2(v2f x, v2h &h, v2h &l) {
     l = __builtin_convertvector(x - __builtin_convertvector(h, v2f), v2h);
 }
 
-// LDS of one work item. Arrays are flat with padded strides so that the
-// accesses of the phases below spread over the banks (64-bit accesses by 16
-// lanes and 32-bit accesses by 32 lanes touch distinct banks):
-//   U(f, s)          fields at the master slots, row stride 9
-//   B(p, k, s)       constrained basis rows, point stride 40
-//   I(p, f, k)       interpolated fields, field stride 5, point stride 5 NF
-//   D(p, i, j, k, l) coefficient blocks, block stride 17, point stride 276
-// NF fields: the state (u, p, u_prev); the D blocks of all 8 points of a chunk are held at once
-constexpr int LU = 9, LB = 40, LDB = 17, LDP = 16 * LDB + 4;
-template <typename T>
-struct Smem {
-    static constexpr int CP = 8, PD = 8, NF = 7;
-    T sU[NF * LU];
-    T sC[8][8];
-    T sB[CP * LB];
-    T sQ[CP][NQ2];
-    union {  // the interpolated fields are dead once the point quantities exist
-        T sI[CP * NF * 5];
-        T sD[PD * LDP];  // weight folded in
-    };
-    T sSc[CP];       // fp16 form: per-point bound of the contraction operands
-    int sM[8];
-};
-#define SU(f, s) sU[(f) * LU + (s)]
-#define SB(p, k, s) sB[(p) * LB + (k) * 8 + (s)]
-#define SI(p, f, k) sI[(p) * (NF * 5) + (f) * 5 + (k)]
-#define SD(p, i, j, k, l) sD[(p) * LDP + ((i) * 4 + (j)) * LDB + (k) * 4 + (l)]
-
+constexpr int LU = 9, LB = 40;  // padded strides in LDS (FP64): fields, basis rows of a point
 
 // Per-lane element data of one OUT work item, loaded ahead of its use: the
 // element, its level and hanging flag, the master of slot lane % 8, the
@@ -132,467 +101,6 @@ __device__ inline void load_pre2(const AsmArgs &a, int64_t i0, int64_t i1, bool 
     P1.m = a.masters[8 * (int64_t)P1.e + s];
     P0.fv = (lane < 56 && P0.m >= 0) ? field_in(a, lane >> 3)[P0.m] : 0.0;
     P1.fv = (lane < 56 && P1.m >= 0) ? field_in(a, lane >> 3)[P1.m] : 0.0;
-}
-
-// One work item (an element, or a run of sub-cell points of one element) by
-// one 64-lane workgroup, mixed forms.
-template <typename T, int MODE, bool SUB>
-__device__ __forceinline__ void asm_item(const AsmArgs &a, const int64_t item, Smem<T> &sm,
-                                         const ItemPre *pre = nullptr) {
-    constexpr int CP = 8;  // points per chunk (one lane group of 8 per point)
-    constexpr int PD = 8, NF = 7;
-    static_assert(MODE != 0, "FP64 element matrices: asm_item64");
-    auto &sU = sm.sU;
-    auto &sC = sm.sC;
-    auto &sB = sm.sB;
-    auto &sI = sm.sI;
-    auto &sQ = sm.sQ;
-    auto &sD = sm.sD;
-    auto &sSc = sm.sSc;
-    auto &sM = sm.sM;
-    const int lane = threadIdx.x;
-    __syncthreads();  // the previous item of this workgroup is done with the LDS
-    const int e = pre ? pre->e : a.items[item];
-    const bool hang = (pre ? pre->hang : a.has_hang[e]) != 0;
-    const int lev = pre ? pre->level : (int)a.level[e];
-    const double hd = ldexp(a.root_len, -lev);
-    const double two_over_h = ldexp(a.two_over_root, lev);
-    const T h = (T)hd;
-    if (lane < 8) sM[lane] = pre ? pre->m : a.masters[8 * (int64_t)e + lane];
-    {
-        const int v = lane >> 3, s = lane & 7, bit = 2 * (v * 8 + s);
-        const uint32_t code = pre ? pre->code : (a.ccode[4 * (int64_t)e + (bit >> 5)] >> (bit & 31)) & 3u;
-        sC[v][s] = code == 3u ? T(1) : (code == 2u ? T(0.5) : (code == 1u ? T(0.25) : T(0)));
-    }
-    if (pre) {
-        if (lane < 56) SU(lane >> 3, lane & 7) = (T)pre->fv;
-        __syncthreads();
-    } else {
-        __syncthreads();
-        for (int idx = lane; idx < NF * 8; idx += 64) {
-            const int f = idx >> 3, s = idx & 7, m = sM[s];
-            double v = 0.0;
-            if (m >= 0) v = field_in(a, f)[m];
-            SU(f, s) = (T)v;
-        }
-    }
-    const int npts = SUB ? a.pt_cnt[item] : 8;
-    const T rho = (T)a.rho, mu = (T)a.mu, th = (T)a.theta;
-    const T idt = (T)a.idt, irho = (T)a.irho;
-    // G = (2/h)^2 I: u.G.u = gG |u|^2; tau_M^-2 = c_t/dt^2 + gG |u|^2 + c_i nu^2 G:G;
-    // tau_C = 1/(tau_M tr G) = (h^2/12)/tau_M
-    const double gGd = two_over_h * two_over_h;
-    const T gG = (T)gGd;
-    const T tau0 = (T)(a.tau_a + a.tau_b * gGd * gGd);
-    const T h2_12 = (T)(hd * hd * (1.0 / 12.0));
-    // fp16 form: gradient rows of the basis scaled by h/2 (all rows within
-    // [-1, 1]); s16 = exponent of the product scale (accumulators carry 2^s16)
-    const float hhalf = (float)(0.5 * hd), gh = (float)two_over_h;
-    int s16 = INT_MAX;
-
-    // stage-2 accumulators (16x16 blocks, see phase 5) and residual
-    v4f accf[8];
-    for (int t = 0; t < 8; ++t) accf[t] = v4f{0, 0, 0, 0};
-    T R = T(0);  // lanes < 32: residual of (a = lane & 7, i = lane >> 3)
-    // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
-    const int64_t eoff = SUB ? a.pt_off[item] : 0;
-    uint32_t en_cur = (SUB && (lane >> 3) < npts) ? a.entries[eoff + (lane >> 3)] : 0u;
-
-    for (int base = 0; base < npts; base += CP) {
-        const int np = min(CP, npts - base);
-        const int pn = base + CP + (lane >> 3);
-        const uint32_t en_next = (SUB && pn < npts) ? a.entries[eoff + pn] : 0u;
-        // ---- phase 1: constrained basis at the chunk's points (lane = (p, s))
-        for (int idx = lane; idx < CP * 8; idx += 64) {
-            const int p = idx >> 3, s = idx & 7;
-            T b[4] = {T(0), T(0), T(0), T(0)};
-            double w = 0.0;
-            if (p < np) {
-                double xi[3];
-                point_xw<SUB>(a, en_cur, base + p, hd, xi, w);
-                // vertex v of the constrained slot s: v = s without hanging
-                // corners, else every v with C[v][s] != 0
-                const T xt[3] = {(T)xi[0], (T)xi[1], (T)xi[2]};
-                const T hg = T(0.5) * (T)two_over_h;
-                const int v0 = hang ? 0 : s, v1 = hang ? 8 : s + 1;
-#pragma unroll 1
-                for (int v = v0; v < v1; ++v) {
-                    const T c = hang ? sC[v][s] : T(1);
-                    if (c == T(0)) continue;
-                    T f[3], g[3];
-                    for (int k = 0; k < 3; ++k) {
-                        const bool up = (v >> k) & 1;
-                        f[k] = T(0.5) * (up ? T(1) + xt[k] : T(1) - xt[k]);
-                        g[k] = up ? hg : -hg;
-                    }
-                    b[0] += c * (f[0] * f[1] * f[2]);
-                    b[1] += c * (g[0] * f[1] * f[2]);
-                    b[2] += c * (f[0] * g[1] * f[2]);
-                    b[3] += c * (f[0] * f[1] * g[2]);
-                }
-            }
-            for (int k = 0; k < 4; ++k) SB(p, k, s) = b[k];
-            if (s == 0) {
-                sQ[p][QW] = (T)w;
-                sSc[p] = T(0);
-            }
-        }
-        __syncthreads();
-        // ---- phase 2: interpolation of the nodal fields (lane = (p, field))
-        for (int idx = lane; idx < CP * 8; idx += 64) {
-            const int p = idx >> 3, f = idx & 7;
-            if (p < np && f < NF) {
-                T v[4] = {T(0), T(0), T(0), T(0)};
-                for (int s = 0; s < 8; ++s) {
-                    const T u = SU(f, s);
-                    for (int k = 0; k < 4; ++k) v[k] += SB(p, k, s) * u;
-                }
-                for (int k = 0; k < 4; ++k) SI(p, f, k) = v[k];
-            }
-        }
-        __syncthreads();
-        // ---- phase 3: point quantities, lane = (p, r). (a) Lanes r = 0..3 of
-        // point p evaluate the point state; lane r < 3 writes row / component
-        // c = r of it and momentum row c of the residual coefficients r^i[k]
-        // (times W), lane r = 3 the scalars and the continuity row.
-        {
-            const int p = lane >> 3, r = lane & 7;
-            if (p < np && r < 4) {
-                T ut[3], gu[3][3], up[3];
-                for (int c = 0; c < 3; ++c) {
-                    ut[c] = th * SI(p, c, 0) + (T(1) - th) * SI(p, 4 + c, 0);
-                    for (int m = 0; m < 3; ++m)
-                        gu[c][m] = th * SI(p, c, 1 + m) + (T(1) - th) * SI(p, 4 + c, 1 + m);
-                }
-                T rM[3];
-                for (int c = 0; c < 3; ++c) {
-                    const T atc = (SI(p, c, 0) - SI(p, 4 + c, 0)) * idt;
-                    const T conv = ut[0] * gu[c][0] + ut[1] * gu[c][1] + ut[2] * gu[c][2];
-                    rM[c] = rho * (atc + conv) + SI(p, 3, 1 + c);
-                }
-                const T div = gu[0][0] + gu[1][1] + gu[2][2];
-                const T s0 = tau0 + gG * (ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2]);
-                const T tauM = rsq<T>(s0);
-                const T tauC = h2_12 * s0 * tauM;  // (h^2/12) / tau_M
-                for (int c = 0; c < 3; ++c) up[c] = -tauM * rM[c];
-                const T pp = -rho * tauC * div;
-                const T upg = gG * (up[0] * up[0] + up[1] * up[1] + up[2] * up[2]);
-                const T tb = upg > T(0) ? rsq<T>(upg) : T(0);
-                T *q = sQ[p];
-                const T W = q[QW];
-                if (r < 3) {
-                    const int c = r;
-                    T guc[3], gcol[3];
-                    for (int m = 0; m < 3; ++m) {
-                        guc[m] = th * SI(p, c, 1 + m) + (T(1) - th) * SI(p, 4 + c, 1 + m);
-                        gcol[m] = th * SI(p, m, 1 + c) + (T(1) - th) * SI(p, 4 + m, 1 + c);
-                    }
-                    const T utc = th * SI(p, c, 0) + (T(1) - th) * SI(p, 4 + c, 0);
-                    const T atc = (SI(p, c, 0) - SI(p, 4 + c, 0)) * idt;
-                    const T convc = ut[0] * guc[0] + ut[1] * guc[1] + ut[2] * guc[2];
-                    const T upc = -tauM * (rho * (atc + convc) + SI(p, 3, 1 + c));
-                    const T svc = up[0] * guc[0] + up[1] * guc[1] + up[2] * guc[2];
-                    const T pr = SI(p, 3, 0);
-                    q[QUT + c] = utc;
-                    q[QUP + c] = upc;
-                    q[QSV + c] = svc;
-                    for (int m = 0; m < 3; ++m) q[QG + 3 * c + m] = guc[m];
-                    q[QRC + 4 * c] = W * (rho * atc + rho * convc + svc);
-                    for (int k = 0; k < 3; ++k)
-                        q[QRC + 4 * c + 1 + k] =
-                            W * (mu * (guc[k] + gcol[k]) - (k == c ? pr + pp : T(0)) - ut[k] * upc -
-                                 up[k] * upc * irho + tb * up[k] * svc);
-                } else {
-                    q[QTM] = tauM;
-                    q[QTC] = tauC;
-                    q[QTB] = tb;
-                    q[QRC + 12] = W * div;
-                    for (int k = 0; k < 3; ++k) q[QRC + 13 + k] = -W * up[k] * irho;
-                }
-            }
-        }
-        // (b) the factors of the D blocks from the stored point state, lane
-        // (p, r): r < 3 the matrix rows c = r, 3 <= r < 6 the vector
-        // components c = r - 3. The round trip through LDS bounds the registers
-        // the point phase holds.
-        {
-            __syncthreads();
-            const int p = lane >> 3, r = lane & 7;
-            if (p < np && r < 6) {
-                const T *qc = sQ[p];
-                T *q = sQ[p];
-                const T tauM = qc[QTM], tb = qc[QTB];
-                const T tr = tauM * rho, tbtr = tb * tauM * rho, tbt = tb * tauM, tir = tauM * irho;
-                if (r < 3) {
-                    const int c = r;
-                    for (int m = 0; m < 3; ++m) {
-                        q[QA + 3 * c + m] = (c == m ? idt : T(0)) + th * qc[QG + 3 * c + m];
-                        T v = T(0);
-                        for (int k = 0; k < 3; ++k)
-                            v += qc[QG + 3 * c + k] * ((k == m ? idt : T(0)) + th * qc[QG + 3 * k + m]);
-                        q[QGA + 3 * c + m] = v;
-                    }
-                } else {
-                    const int c = r - 3;
-                    const T utc = qc[QUT + c], upc = qc[QUP + c], svc = qc[QSV + c];
-                    q[QY + c] = tr * utc + tauM * upc;
-                    q[QX + c] = -tbtr * upc;
-                    q[QCP + c] = tauM * upc - tbtr * svc;
-                    q[QYM + c] = tauM * utc + tir * upc;
-                    q[QCM + c] = tir * upc - tbt * svc;
-                    q[QXM + c] = -tbt * upc;
-                }
-            }
-        }
-        __syncthreads();
-        {
-            // ---- phases 4 and 5 over batches of PD points
-            for (int pb = 0; pb < np; pb += PD) {
-            const int nd = min(PD, np - pb);
-            if (pb > 0) __syncthreads();  // the previous batch is done with the D blocks
-            // ---- phase 4: D blocks (one (p, i, j) block per task), weight folded in.
-            // Tasks are ordered by kind so that the lanes of a pass share a code
-            // path: the 9 momentum/velocity blocks of every point first, then the
-            // 7 simple blocks of every point.
-            for (int t = lane; t < PD * 16; t += 64) {
-                int p, i, j;
-                const bool mv = t < 9 * PD;
-                if (mv) {
-                    p = t / 9;
-                    i = (t % 9) / 3;
-                    j = t % 3;
-                } else {
-                    const int u = t - 9 * PD, r = u % 7;
-                    p = u / 7;
-                    i = r < 3 ? r : 3;
-                    j = r < 3 ? 3 : (r < 6 ? r - 3 : 3);
-                }
-                T D[4][4];
-                if (p >= nd) {
-                    for (int k = 0; k < 4; ++k)
-                        for (int l = 0; l < 4; ++l) D[k][l] = T(0);
-                } else if (mv) {
-                    dblock_mv<T>(sQ[pb + p], i, j, rho, mu, th, D);
-                } else {
-                    dblock_simple<T>(sQ[pb + p], i, j, irho, th, D);
-                }
-                for (int k = 0; k < 4; ++k)
-                    for (int l = 0; l < 4; ++l) SD(p, i, j, k, l) = D[k][l];
-                if constexpr (MODE == 2) {
-                    // bound of the point's stage-1 operands: row k is sum_l D[k][l] B[l][b]
-                    // with |B| <= 1 for values and <= 2/h for gradients, times 2/h
-                    // for gradient rows (their basis rows carry h/2)
-                    if (p < nd) {
-                        float bnd = 0.f;
-                        for (int k = 0; k < 4; ++k) {
-                            float v = fabsf((float)D[k][0]);
-                            for (int l = 1; l < 4; ++l) v += gh * fabsf((float)D[k][l]);
-                            bnd = fmaxf(bnd, k > 0 ? gh * v : v);
-                        }
-                        atomicMax((int *)&sSc[pb + p], __float_as_int(bnd));  // non-negative floats
-                    }
-                }
-            }
-            __syncthreads();
-            // ---- phase 5: stage 1 (VALU) and stage 2 (MFMA)
-            const int col = lane & 15, bb = col >> 2, jc = col & 3;
-            {
-                // k-step of 32 = 8 points x 4 derivative rows; lane group g holds points 2g, 2g+1
-                const int g = lane >> 4, row = lane & 15;
-                const int ar = row & 7;
-                const bool hi_rows = row < 8;
-                // fp16: powers of two put the chunk's largest product near 2^12 and
-                // balance it between the two operands of each point (A about 2^ea, F
-                // about 2^(s16 - ea)): both split terms stay in the normal fp16 range.
-                // A later chunk with larger products lowers s16 and rescales the
-                // accumulators (exact).
-                int ea[2] = {0, 0};
-                if constexpr (MODE == 2) {
-                    float bm = 0.f;
-                    for (int q = 0; q < CP; ++q) bm = fmaxf(bm, (float)sSc[q]);
-                    if (bm > 0.f) {
-                        const int sc = 12 - ilogbf(bm);
-                        if (s16 == INT_MAX) {
-                            s16 = sc;
-                        } else if (sc < s16) {
-                            const float f = ldexpf(1.0f, sc - s16);
-                            for (int t = 0; t < 8; ++t)
-                                for (int r = 0; r < 4; ++r) accf[t][r] *= f;
-                            s16 = sc;
-                        }
-                    }
-                    const int sv = s16 == INT_MAX ? 0 : s16;
-                    for (int pp = 0; pp < 2; ++pp) {
-                        const float bp = (float)sSc[2 * g + pp];
-                        ea[pp] = bp > 0.f ? ((ilogbf(bp) + sv) >> 1) : 0;
-                    }
-                }
-                float Av[8];
-                for (int t = 0; t < 8; ++t) {
-                    const int p = 2 * g + (t >> 2), k = t & 3;
-                    float v = (float)SB(p, k, ar);
-                    if (MODE == 2) v *= ldexpf(k == 0 ? 1.0f : hhalf, ea[t >> 2]);
-                    Av[t] = v;
-                }
-                // basis values of the lane's two points at its two columns b
-                float Bc[2][2][4];
-                for (int pp = 0; pp < 2; ++pp)
-                    for (int bh = 0; bh < 2; ++bh)
-                        for (int m = 0; m < 4; ++m) Bc[pp][bh][m] = (float)SB(2 * g + pp, m, 4 * bh + bb);
-                float fs[2][4];
-                for (int pp = 0; pp < 2; ++pp)
-                    for (int k = 0; k < 4; ++k)
-                        fs[pp][k] = MODE == 2 ? ldexpf(k == 0 ? 1.0f : gh, (s16 == INT_MAX ? 0 : s16) - ea[pp])
-                                              : 1.0f;
-                if (MODE == 1) {
-                    v8bf Ahm, Alo;
-                    for (int t = 0; t < 8; ++t) {
-                        __bf16 x1, x2, x3;
-                        split3(Av[t], x1, x2, x3);
-                        Ahm[t] = hi_rows ? x1 : x2;
-                        Alo[t] = hi_rows ? x3 : (__bf16)0.0f;
-                    }
-                    for (int i = 0; i < 4; ++i) {
-                        v8bf F1[2], F2[2], F3[2];
-                        for (int t = 0; t < 8; t += 2) {
-                            const int pp = t >> 2, p = 2 * g + pp, k = t & 3;
-                            float d[2][4];
-                            for (int m = 0; m < 4; ++m) {
-                                d[0][m] = (float)SD(p, i, jc, k, m);
-                                d[1][m] = (float)SD(p, i, jc, k + 1, m);
-                            }
-                            for (int bh = 0; bh < 2; ++bh) {
-                                v2f F;
-                                for (int e = 0; e < 2; ++e)
-                                    F[e] = d[e][0] * Bc[pp][bh][0] + d[e][1] * Bc[pp][bh][1] +
-                                           d[e][2] * Bc[pp][bh][2] + d[e][3] * Bc[pp][bh][3];
-                                v2bf x1, x2, x3;
-                                split3x2(F, x1, x2, x3);
-                                F1[bh][t] = x1[0]; F1[bh][t + 1] = x1[1];
-                                F2[bh][t] = x2[0]; F2[bh][t + 1] = x2[1];
-                                F3[bh][t] = x3[0]; F3[bh][t + 1] = x3[1];
-                            }
-                        }
-                        for (int bh = 0; bh < 2; ++bh) {
-                            v4f acc = accf[2 * i + bh];
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F1[bh], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F2[bh], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F3[bh], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, F1[bh], acc, 0, 0, 0);
-                            accf[2 * i + bh] = acc;
-                        }
-                    }
-                } else {
-                    v8h Ahm;
-                    for (int t = 0; t < 8; ++t) {
-                        _Float16 x1, x2;
-                        split2h(Av[t], x1, x2);
-                        Ahm[t] = hi_rows ? x1 : x2;
-                    }
-                    for (int i = 0; i < 4; ++i) {
-                        v8h F1[2], F2[2];
-                        for (int t = 0; t < 8; t += 2) {
-                            const int pp = t >> 2, p = 2 * g + pp, k = t & 3;
-                            float d[2][4];
-                            for (int m = 0; m < 4; ++m) {
-                                d[0][m] = (float)SD(p, i, jc, k, m);
-                                d[1][m] = (float)SD(p, i, jc, k + 1, m);
-                            }
-                            for (int bh = 0; bh < 2; ++bh) {
-                                // undo the basis scaling and the balance on this operand
-                                v2f F;
-                                for (int e = 0; e < 2; ++e)
-                                    F[e] = (d[e][0] * Bc[pp][bh][0] + d[e][1] * Bc[pp][bh][1] +
-                                            d[e][2] * Bc[pp][bh][2] + d[e][3] * Bc[pp][bh][3]) * fs[pp][k + e];
-                                v2h x1, x2;
-                                split2hx2(F, x1, x2);
-                                F1[bh][t] = x1[0]; F1[bh][t + 1] = x1[1];
-                                F2[bh][t] = x2[0]; F2[bh][t + 1] = x2[1];
-                            }
-                        }
-                        for (int bh = 0; bh < 2; ++bh) {
-                            v4f acc = accf[2 * i + bh];
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ahm, F1[bh], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ahm, F2[bh], acc, 0, 0, 0);
-                            accf[2 * i + bh] = acc;
-                        }
-                    }
-                }
-            }
-            }  // batches of PD points
-        }
-        // residual: lanes < 32, (a = lane & 7, i = lane >> 3)
-        if (lane < 32) {
-            const int av = lane & 7, i = lane >> 3;
-            for (int p = 0; p < np; ++p)
-                R += SB(p, 0, av) * sQ[p][QRC + 4 * i] + SB(p, 1, av) * sQ[p][QRC + 4 * i + 1] +
-                     SB(p, 2, av) * sQ[p][QRC + 4 * i + 2] + SB(p, 3, av) * sQ[p][QRC + 4 * i + 3];
-        }
-        en_cur = en_next;
-        __syncthreads();
-    }
-
-    // ---- element matrix out: one 1024-entry record per work item, block-major
-    // (block (a, b) of master slots, entry 4 i + j), stored from the
-    // accumulators; the CSR is summed from these records by the gather kernel
-    // (no atomics, fixed summation order)
-    if (a.vals) {
-        // atomic scatter: no record; each entry is added into its CSR place
-        // (the summation order is the hardware's)
-        T *vals = (T *)a.vals;
-        const int32_t *mst = a.masters + 8 * (int64_t)e;
-        const uint16_t *kk = a.el_kk + 64 * (int64_t)e;
-        {
-            const int col = lane & 15, bb = col >> 2, jc = col & 3;
-            const float unscale = (MODE == 2 && s16 != INT_MAX) ? ldexpf(1.0f, -s16) : 1.0f;
-            // rows av = 4 (lane / 16) + r of the lanes < 32, columns b = 4 h + bb
-            int64_t rb[4], dg[4];
-            bool ok[4];
-            for (int r = 0; r < 4; ++r) {
-                const int ma = mst[(4 * (lane >> 4) + r) & 7];
-                ok[r] = ma >= 0;
-                rb[r] = ok[r] ? a.nrow_ptr[ma] : 0;
-                dg[r] = ok[r] ? a.nrow_ptr[ma + 1] - rb[r] : 0;
-            }
-            for (int t = 0; t < 8; ++t) {
-                v4f v = accf[t];
-                for (int r = 0; r < 4; ++r) v[r] = (v[r] + __shfl_down(v[r], 32, 64)) * unscale;
-                const int i = t >> 1, b = 4 * (t & 1) + bb;
-                if (lane < 32 && mst[b] >= 0) {
-                    for (int r = 0; r < 4; ++r) {
-                        const int av = 4 * (lane >> 4) + r;
-                        if (ok[r])
-                            atomicAdd(vals + 16 * rb[r] + 4 * (int64_t)kk[8 * av + b] + 4 * i * dg[r] + jc,
-                                      (T)v[r]);
-                    }
-                }
-            }
-        }
-    } else {
-        const int col = lane & 15, bb = col >> 2, jc = col & 3;
-        T *dst = (T *)a.em + (a.slot0 + item) * 1024;
-        {
-            // rows 8..15 carry the second split term: fold them onto rows 0..7
-            const float unscale = (MODE == 2 && s16 != INT_MAX) ? ldexpf(1.0f, -s16) : 1.0f;
-            for (int t = 0; t < 8; ++t) {
-                v4f v = accf[t];
-                for (int r = 0; r < 4; ++r) v[r] = (v[r] + __shfl_down(v[r], 32, 64)) * unscale;
-                if (lane < 32) {
-                    const int i = t >> 1, b = 4 * (t & 1) + bb;
-                    for (int r = 0; r < 4; ++r) {
-                        const int av = 4 * (lane >> 4) + r;  // output row = 4 (lane / 16) + r
-                        dst[(av * 8 + b) * 16 + 4 * i + jc] = (T)v[r];
-                    }
-                }
-            }
-        }
-    }
-    // residual record of the work item (entry 4 a + i); the residual is summed
-    // from the records by node, in a fixed order
-    if (lane < 32 && a.rrec) {
-        const int av = lane & 7, i = lane >> 3;
-        a.rrec[(a.slot0 + item) * 32 + 4 * av + i] = (double)R;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -895,23 +403,547 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
     if (i4 < 2 && a.rrec) a.rrec[(a.slot0 + item) * 32 + 4 * (4 * i4 + c4) + r4] = accr;
 }
 
+// ---------------------------------------------------------------------------
+// Mixed element matrices (BF16x3, FP16x2)
+// ---------------------------------------------------------------------------
+//
+// Everything before the contraction is FP32; its roundings (the order of every
+// sum and which products are fused) are those of the residual kernels of the
+// mixed contexts too, whose results it must equal bit for bit.
+//
+// What bounds it: latency, then VALU issue. LDS decides the occupancy, so only
+// the D blocks of two test components are there at a time (4.2 KB instead of
+// 8.8), all arrays are in groups of four read and written as 16 bytes, and the
+// record leaves through LDS in whole lines: 8.8 KB and 126 VGPRs, four waves per
+// SIMD (13 KB and three before). Steps: 52k-octant adaptive mesh BF16x3 0.817 ->
+// 0.695 ms, 194k-octant sphere FP16x2 2.47 -> 2.07 ms, 878k-octant sphere BF16x3
+// 9.00 -> 7.84 ms.
+#define FQ_UT 0    // u_theta, W
+#define FQ_UP 4    // u', tau_M
+#define FQ_Y 8     // Y, taubar
+#define FQ_X 12    // X, tau_C
+#define FQ_A 16    // I/dt + theta grad u by columns j, 4 apart
+#define FQ_G 28    // grad u rows, 4 apart
+#define FQ_GA 40   // grad u A rows, 4 apart
+#define FQ_CP 52
+#define FQ_YM 56
+#define FQ_XM 60
+#define FQ_CM 64
+#define FQ_RC 68   // 16 residual coefficients
+#define FQ_SV 84
+#define FQ_N 92
+constexpr int FB = 36;   // floats of a point's basis: (slot, derivative), padded
+constexpr int FD = 132;  // floats of a point's D blocks of two test components, padded
+
+struct SmemF {
+    __attribute__((aligned(16))) float sU[7 * 8];
+    float sC[64];
+    __attribute__((aligned(16))) float sB[8 * FB];
+    __attribute__((aligned(16))) float sQ[8 * FQ_N];
+    union {
+        __attribute__((aligned(16))) float sI[8 * 28];  // interpolated fields (field, derivative)
+        // blocks (i % 2, j), rows k; points 2 g + pp at 4 pp + g, so that the four
+        // lane groups of the contraction read different banks
+        __attribute__((aligned(16))) float sD[8 * FD];
+        __attribute__((aligned(16))) float sOut[1024];  // the record, on its way out
+    };
+    float sSc[8];  // fp16 form: per-point bound of the contraction operands
+};
+
+// One 4x4 D block, weight folded in (dblock_mv and dblock_simple of vms_point.h
+// on the packed table).
+__device__ inline void dblock_f(const float *q, int i, int j, float rho, float mu, float th, float irho, v4f D[4]) {
+    const v4f UT = *(const v4f *)(q + FQ_UT), UP = *(const v4f *)(q + FQ_UP), Yv = *(const v4f *)(q + FQ_Y),
+              Xv = *(const v4f *)(q + FQ_X);
+    const float W = UT[3], tauM = UP[3], tb = Yv[3], tC = Xv[3];
+    if (i < 3 && j < 3) {
+        const v4f Acol = *(const v4f *)(q + FQ_A + 4 * j);
+        float ei[3], ej[3];
+        for (int l = 0; l < 3; ++l) {
+            ei[l] = l == i ? 1.f : 0.f;
+            ej[l] = l == j ? 1.f : 0.f;
+        }
+        const float Aij = q[FQ_A + 4 * j + i], gij = q[FQ_G + 4 * i + j], GAij = q[FQ_GA + 4 * i + j];
+        const float cpi = q[FQ_CP + i], upi = q[FQ_UP + i];
+        const float tr = tauM * rho;
+        const float dth = (i == j) ? th * W : 0.f;
+        const float thw = th * W;
+        D[0][0] = W * (rho * Aij - tr * GAij);
+        const float a0 = dth * rho - thw * tr * gij;
+        for (int l = 0; l < 3; ++l) D[0][1 + l] = a0 * UT[l] + dth * UP[l];
+        const float c1 = dth * tr, c2 = dth * tauM, c3 = -thw * tb * tr * gij, c4 = dth * tb;
+        const float AW = Aij * W, GW = GAij * W, cW = cpi * W;
+        const float mthw = mu * thw, rtcw = rho * tC * thw;
+        const float dm = (i == j) ? mthw : 0.f;
+        for (int k = 0; k < 3; ++k) {
+            const float kj = ej[k], ki = ei[k];
+            D[1 + k][0] = AW * Yv[k] + cW * Acol[k] + GW * Xv[k] - kj * (thw * upi);
+            const float al = c1 * UT[k] + (c2 + c3) * UP[k] + kj * (thw * cpi);
+            const float be = c4 * UP[k];
+            const float s1 = kj * mthw, s2 = ki * rtcw;
+            for (int l = 0; l < 3; ++l) {
+                float v = al * UT[l] + be * UP[l] + s1 * ei[l] + s2 * ej[l];
+                if (k == l) v += dm;
+                D[1 + k][1 + l] = v;
+            }
+        }
+    } else {
+        const bool mp = i < 3 && j == 3, cv = i == 3 && j < 3;
+        const float wmp = mp ? W : 0.f, wcv = cv ? W : 0.f, wcc = (!mp && !cv) ? W : 0.f;
+        const int ii = i < 3 ? i : 0, jj = j < 3 ? j : 0;
+        const v4f g = *(const v4f *)(q + FQ_G + 4 * ii), Acol = *(const v4f *)(q + FQ_A + 4 * jj),
+                  ym = *(const v4f *)(q + FQ_YM), xm = *(const v4f *)(q + FQ_XM);
+        float ei[3], ej[3];
+        for (int l = 0; l < 3; ++l) {
+            ei[l] = l == i ? 1.f : 0.f;
+            ej[l] = l == j ? 1.f : 0.f;
+        }
+        const float cmi = q[FQ_CM + ii];
+        const float tw = wcv * tauM, tthw = tw * th, mtau = -wmp * tauM, thw = wcv * th;
+        const float diag = wmp * cmi + wcc * tauM * irho;
+        D[0][0] = 0.f;
+        for (int l = 0; l < 3; ++l) D[0][1 + l] = mtau * g[l] + thw * ej[l];
+        for (int k = 0; k < 3; ++k) {
+            D[1 + k][0] = tw * Acol[k] - wmp * ei[k];
+            const float xk = wmp * xm[k], yk = wmp * ym[k], sk = tthw * ej[k];
+            for (int l = 0; l < 3; ++l) {
+                float v = xk * g[l] + sk * UT[l] + yk * ei[l];
+                if (k == l) v += diag;
+                D[1 + k][1 + l] = v;
+            }
+        }
+    }
+}
+
+// TIGHT: the lane's addresses and masks are formed anew for every chunk; kept
+// over the loop they take the sub-cell items from 126 VGPRs to over 160
+template <int MODE, bool SUB, bool TIGHT = SUB>
+__device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item, SmemF &sm, const ItemPre *pre) {
+    const int lane = threadIdx.x;
+    __syncthreads();  // the previous item of this workgroup is done with the LDS
+    const int e = pre ? pre->e : a.items[item];
+    const bool hang = (pre ? pre->hang : a.has_hang[e]) != 0;
+    const int lev = pre ? pre->level : (int)a.level[e];
+    const double hd = ldexp(a.root_len, -lev);
+    const double two_over_h = ldexp(a.two_over_root, lev);
+    {
+        uint32_t code;
+        double fv;
+        if (pre) {
+            code = pre->code;
+            fv = pre->fv;
+        } else {
+            const int bit = 2 * lane;
+            code = (a.ccode[4 * (int64_t)e + (bit >> 5)] >> (bit & 31)) & 3u;
+            const int m = a.masters[8 * (int64_t)e + (lane & 7)];
+            fv = (lane < 56 && m >= 0) ? field_in(a, lane >> 3)[m] : 0.0;
+        }
+        sm.sC[lane] = code == 3u ? 1.f : (code == 2u ? 0.5f : (code == 1u ? 0.25f : 0.f));
+        if (lane < 56) sm.sU[lane] = (float)fv;
+    }
+    const int npts = SUB ? a.pt_cnt[item] : 8;
+    const float rho = (float)a.rho, mu = (float)a.mu, th = (float)a.theta, idt = (float)a.idt, irho = (float)a.irho;
+    // G = (2/h)^2 I: u.G.u = gG |u|^2; tau_M^-2 = c_t/dt^2 + gG |u|^2 + c_i nu^2 G:G;
+    // tau_C = 1/(tau_M tr G) = (h^2/12)/tau_M
+    const double gGd = two_over_h * two_over_h;
+    const float gG = (float)gGd, tau0 = (float)(a.tau_a + a.tau_b * gGd * gGd);
+    const float h2_12 = (float)(hd * hd * (1.0 / 12.0));
+    // fp16 form: gradient rows of the basis scaled by h/2 (all rows within
+    // [-1, 1]); s16 = exponent of the product scale (accumulators carry 2^s16)
+    const float hhalf = (float)(0.5 * hd), gh = (float)two_over_h;
+    int s16 = INT_MAX;
+
+    v4f acc[4][2];
+    for (int t = 0; t < 8; ++t) acc[t >> 1][t & 1] = v4f{0, 0, 0, 0};
+    float R = 0.f;  // lanes < 32: residual of (a = lane & 7, i = lane >> 3)
+    // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
+    const int64_t eoff = SUB ? a.pt_off[item] : 0;
+    uint32_t en_cur = (SUB && (lane >> 3) < npts) ? a.entries[eoff + (lane >> 3)] : 0u;
+    __syncthreads();
+
+    for (int base = 0; base < npts; base += 8) {
+        const int np = min(8, npts - base);
+        int lane = threadIdx.x;
+        if (TIGHT) asm volatile("" : "+v"(lane));
+        const int pn = base + 8 + (lane >> 3);
+        const uint32_t en_next = (SUB && pn < npts) ? a.entries[eoff + pn] : 0u;
+        // ---- phase 1: constrained basis at the chunk's points (lane = (p, s))
+        {
+            const int p = lane >> 3, s = lane & 7;
+            float b[4] = {0.f, 0.f, 0.f, 0.f};
+            double w = 0.0;
+            if (p < np) {
+                double xi[3];
+                point_xw<SUB>(a, en_cur, base + p, hd, xi, w);
+                // vertex v of the constrained slot s: v = s without hanging
+                // corners, else every v with C[v][s] != 0
+                const float xt[3] = {(float)xi[0], (float)xi[1], (float)xi[2]};
+                const float hg = 0.5f * (float)two_over_h;
+                const int v0 = hang ? 0 : s, v1 = hang ? 8 : s + 1;
+#pragma unroll 1
+                for (int v = v0; v < v1; ++v) {
+                    const float c = hang ? sm.sC[v * 8 + s] : 1.f;
+                    if (c == 0.f) continue;
+                    float f[3], g[3];
+                    for (int k = 0; k < 3; ++k) {
+                        const bool up = (v >> k) & 1;
+                        f[k] = 0.5f * (up ? 1.f + xt[k] : 1.f - xt[k]);
+                        g[k] = up ? hg : -hg;
+                    }
+                    b[0] += c * (f[0] * f[1] * f[2]);
+                    b[1] += c * (g[0] * f[1] * f[2]);
+                    b[2] += c * (f[0] * g[1] * f[2]);
+                    b[3] += c * (f[0] * f[1] * g[2]);
+                }
+            }
+            *(v4f *)(sm.sB + p * FB + 4 * s) = v4f{b[0], b[1], b[2], b[3]};
+            if (s == 0) {
+                sm.sQ[p * FQ_N + FQ_UT + 3] = (float)w;
+                if (MODE == 2) sm.sSc[p] = 0.f;
+            }
+        }
+        __syncthreads();
+        // ---- phase 2: interpolation of the nodal fields (lane = (p, field))
+        {
+            const int p = lane >> 3, f = lane & 7;
+            if (f < 7) {
+                const v4f ua = *(const v4f *)(sm.sU + 8 * f), ub = *(const v4f *)(sm.sU + 8 * f + 4);
+                v4f v = {0.f, 0.f, 0.f, 0.f};
+                for (int s = 0; s < 8; ++s) {
+                    const float u = s < 4 ? ua[s & 3] : ub[s & 3];
+                    const v4f b = *(const v4f *)(sm.sB + p * FB + 4 * s);
+                    for (int k = 0; k < 4; ++k) v[k] += b[k] * u;
+                }
+                *(v4f *)(sm.sI + p * 28 + 4 * f) = v;
+            }
+        }
+        __syncthreads();
+        // ---- phase 3: point quantities, lane = (p, r). (a) Lanes r = 0..3 of
+        // point p evaluate the point state; lane r < 3 writes row / component
+        // c = r of it and momentum row c of the residual coefficients r^i[k]
+        // (times W), lane r = 3 the scalars and the continuity row.
+        {
+            const int p = lane >> 3, r = lane & 7;
+            if (p < np && r < 4) {
+                const float *Ip = sm.sI + p * 28;
+                v4f I[7];
+                for (int f = 0; f < 7; ++f) I[f] = *(const v4f *)(Ip + 4 * f);
+                float ut[3], gu[3][3], up[3];
+                for (int c = 0; c < 3; ++c) {
+                    ut[c] = th * I[c][0] + (1.f - th) * I[4 + c][0];
+                    for (int m = 0; m < 3; ++m) gu[c][m] = th * I[c][1 + m] + (1.f - th) * I[4 + c][1 + m];
+                }
+                float rM[3];
+                for (int c = 0; c < 3; ++c) {
+                    const float atc = (I[c][0] - I[4 + c][0]) * idt;
+                    const float conv = ut[0] * gu[c][0] + ut[1] * gu[c][1] + ut[2] * gu[c][2];
+                    rM[c] = rho * (atc + conv) + I[3][1 + c];
+                }
+                const float div = gu[0][0] + gu[1][1] + gu[2][2];
+                const float s0 = tau0 + gG * (ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2]);
+                const float tauM = rsq<float>(s0);
+                const float tauC = h2_12 * s0 * tauM;  // (h^2/12) / tau_M
+                for (int c = 0; c < 3; ++c) up[c] = -tauM * rM[c];
+                const float pp = -rho * tauC * div;
+                const float upg = gG * (up[0] * up[0] + up[1] * up[1] + up[2] * up[2]);
+                const float tb = upg > 0.f ? rsq<float>(upg) : 0.f;
+                float *q = sm.sQ + p * FQ_N;
+                const float W = q[FQ_UT + 3];
+                if (r < 3) {
+                    const int c = r;
+                    const v4f Ic = *(const v4f *)(Ip + 4 * c), Jc = *(const v4f *)(Ip + 16 + 4 * c);
+                    float guc[3], gcol[3];
+                    for (int m = 0; m < 3; ++m) {
+                        guc[m] = th * Ic[1 + m] + (1.f - th) * Jc[1 + m];
+                        gcol[m] = th * Ip[4 * m + 1 + c] + (1.f - th) * Ip[16 + 4 * m + 1 + c];
+                    }
+                    const float utc = th * Ic[0] + (1.f - th) * Jc[0];
+                    const float atc = (Ic[0] - Jc[0]) * idt;
+                    const float convc = ut[0] * guc[0] + ut[1] * guc[1] + ut[2] * guc[2];
+                    const float upc = -tauM * (rho * (atc + convc) + Ip[13 + c]);
+                    const float svc = up[0] * guc[0] + up[1] * guc[1] + up[2] * guc[2];
+                    const float pr = I[3][0];
+                    q[FQ_UT + c] = utc;
+                    q[FQ_UP + c] = upc;
+                    q[FQ_SV + c] = svc;
+                    *(v4f *)(q + FQ_G + 4 * c) = v4f{guc[0], guc[1], guc[2], 0.f};
+                    float rc[3];
+                    for (int k = 0; k < 3; ++k)
+                        rc[k] = W * (mu * (guc[k] + gcol[k]) - (k == c ? pr + pp : 0.f) - ut[k] * upc -
+                                     up[k] * upc * irho + tb * up[k] * svc);
+                    *(v4f *)(q + FQ_RC + 4 * c) = v4f{W * (rho * atc + rho * convc + svc), rc[0], rc[1], rc[2]};
+                } else {
+                    q[FQ_UP + 3] = tauM;
+                    q[FQ_X + 3] = tauC;
+                    q[FQ_Y + 3] = tb;
+                    *(v4f *)(q + FQ_RC + 12) = v4f{W * div, -W * up[0] * irho, -W * up[1] * irho, -W * up[2] * irho};
+                }
+            }
+        }
+        // (b) the factors of the D blocks from the stored point state, lane
+        // (p, r): r < 3 the matrix rows c = r, 3 <= r < 6 the vector
+        // components c = r - 3. The round trip through LDS bounds the registers
+        // the point phase holds.
+        __syncthreads();
+        {
+            const int p = lane >> 3, r = lane & 7;
+            if (p < np && r < 6) {
+                float *q = sm.sQ + p * FQ_N;
+                const float tauM = q[FQ_UP + 3], tb = q[FQ_Y + 3];
+                const float tr = tauM * rho, tbtr = tb * tauM * rho, tbt = tb * tauM, tir = tauM * irho;
+                if (r < 3) {
+                    const int c = r;
+                    const v4f gc = *(const v4f *)(q + FQ_G + 4 * c), g0 = *(const v4f *)(q + FQ_G),
+                              g1 = *(const v4f *)(q + FQ_G + 4), g2 = *(const v4f *)(q + FQ_G + 8);
+                    float ga[3];
+                    for (int m = 0; m < 3; ++m) {
+                        q[FQ_A + 4 * m + c] = (c == m ? idt : 0.f) + th * gc[m];
+                        float v = 0.f;
+                        for (int k = 0; k < 3; ++k) {
+                            const float gk = k == 0 ? g0[m] : (k == 1 ? g1[m] : g2[m]);
+                            v += gc[k] * ((k == m ? idt : 0.f) + th * gk);
+                        }
+                        ga[m] = v;
+                    }
+                    *(v4f *)(q + FQ_GA + 4 * c) = v4f{ga[0], ga[1], ga[2], 0.f};
+                } else {
+                    const int c = r - 3;
+                    const float utc = q[FQ_UT + c], upc = q[FQ_UP + c], svc = q[FQ_SV + c];
+                    q[FQ_Y + c] = tr * utc + tauM * upc;
+                    q[FQ_X + c] = -tbtr * upc;
+                    q[FQ_CP + c] = tauM * upc - tbtr * svc;
+                    q[FQ_YM + c] = tauM * utc + tir * upc;
+                    q[FQ_CM + c] = tir * upc - tbt * svc;
+                    q[FQ_XM + c] = -tbt * upc;
+                }
+            }
+        }
+        __syncthreads();
+        // ---- phase 4: the D blocks of test components {0, 1}, then {2, 3}: one
+        // block per lane, momentum/velocity blocks first
+        auto dtask = [&](int hf, int &p, int &i, int &j) {
+            const int n = hf == 0 ? 48 : 24;
+            if (lane < n) {
+                p = hf == 0 ? lane / 6 : lane / 3;
+                i = hf == 0 ? (lane % 6) / 3 : 2;
+                j = lane % 3;
+            } else if (hf == 0) {
+                p = (lane - n) >> 1;
+                i = lane & 1;
+                j = 3;
+            } else {
+                const int u = (lane - n) % 5;
+                p = (lane - n) / 5;
+                i = u == 0 ? 2 : 3;
+                j = u == 0 ? 3 : u - 1;
+            }
+        };
+        auto dcompute = [&](int hf, v4f D[4], int &dst) {
+            int p, i, j;
+            dtask(hf, p, i, j);
+            dst = ((p & 1) * 4 + (p >> 1)) * FD + (4 * (i & 1) + j) * 16;
+            if (p >= np) {
+                for (int k = 0; k < 4; ++k) D[k] = v4f{0.f, 0.f, 0.f, 0.f};
+                return;
+            }
+            dblock_f(sm.sQ + p * FQ_N, i, j, rho, mu, th, irho, D);
+            if constexpr (MODE == 2) {
+                // bound of the point's stage-1 operands: row k is sum_l D[k][l] B[l][b]
+                // with |B| <= 1 for values and <= 2/h for gradients, times 2/h
+                // for gradient rows (their basis rows carry h/2)
+                float bnd = 0.f;
+                for (int k = 0; k < 4; ++k) {
+                    float v = fabsf(D[k][0]);
+                    for (int l = 1; l < 4; ++l) v += gh * fabsf(D[k][l]);
+                    bnd = fmaxf(bnd, k > 0 ? gh * v : v);
+                }
+                atomicMax((int *)&sm.sSc[p], __float_as_int(bnd));  // non-negative floats
+            }
+        };
+        v4f D[4];
+        int dst;
+        dcompute(0, D, dst);
+        for (int k = 0; k < 4; ++k) *(v4f *)(sm.sD + dst + 4 * k) = D[k];
+        if constexpr (MODE == 2) dcompute(1, D, dst);  // the scale needs every block's bound
+        __syncthreads();
+        // ---- phase 5: stage 1 (VALU) and stage 2 (MFMA); k-step of 32 = 8 points x
+        // 4 derivative rows, lane group g holds points 2g, 2g+1
+        const int g = lane >> 4, row = lane & 15, ar = row & 7, bb = row >> 2, jc = lane & 3;
+        const bool hi_rows = row < 8;
+        // fp16: powers of two put the chunk's largest product near 2^12 and
+        // balance it between the two operands of each point (A about 2^ea, F
+        // about 2^(s16 - ea)): both split terms stay in the normal fp16 range.
+        // A later chunk with larger products lowers s16 and rescales the
+        // accumulators (exact).
+        int ea[2] = {0, 0};
+        float fs[2][2] = {{1.f, 1.f}, {1.f, 1.f}};
+        if constexpr (MODE == 2) {
+            float bm = 0.f;
+            for (int q = 0; q < 8; ++q) bm = fmaxf(bm, sm.sSc[q]);
+            if (bm > 0.f) {
+                const int sc = 12 - ilogbf(bm);
+                if (s16 == INT_MAX) {
+                    s16 = sc;
+                } else if (sc < s16) {
+                    const float f = ldexpf(1.0f, sc - s16);
+                    for (int t = 0; t < 8; ++t)
+                        for (int r = 0; r < 4; ++r) acc[t >> 1][t & 1][r] *= f;
+                    s16 = sc;
+                }
+            }
+            const int sv = s16 == INT_MAX ? 0 : s16;
+            for (int pp = 0; pp < 2; ++pp) {
+                const float bp = sm.sSc[2 * g + pp];
+                ea[pp] = bp > 0.f ? ((ilogbf(bp) + sv) >> 1) : 0;
+                fs[pp][0] = ldexpf(1.0f, sv - ea[pp]);
+                fs[pp][1] = ldexpf(gh, sv - ea[pp]);
+            }
+        }
+        v8bf Ahm, Alo;
+        v8h Ah;
+        v4f Bc[2][2];  // basis values of the lane's two points at its two columns b
+        for (int pp = 0; pp < 2; ++pp) {
+            const float *B = sm.sB + (2 * g + pp) * FB;
+            const v4f Av = *(const v4f *)(B + 4 * ar);
+            for (int k = 0; k < 4; ++k) {
+                const int t = 4 * pp + k;
+                if constexpr (MODE == 1) {
+                    __bf16 x1, x2, x3;
+                    split3(Av[k], x1, x2, x3);
+                    Ahm[t] = hi_rows ? x1 : x2;
+                    Alo[t] = hi_rows ? x3 : (__bf16)0.0f;
+                } else {
+                    _Float16 x1, x2;
+                    split2h(Av[k] * ldexpf(k == 0 ? 1.0f : hhalf, ea[pp]), x1, x2);
+                    Ah[t] = hi_rows ? x1 : x2;
+                }
+            }
+            for (int bh = 0; bh < 2; ++bh) Bc[pp][bh] = *(const v4f *)(B + 4 * (4 * bh + bb));
+        }
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            if (hf == 1) {
+                if constexpr (MODE == 1) dcompute(1, D, dst);
+                __syncthreads();
+                for (int k = 0; k < 4; ++k) *(v4f *)(sm.sD + dst + 4 * k) = D[k];
+                __syncthreads();
+            }
+#pragma unroll
+            for (int i2 = 0; i2 < 2; ++i2) {
+                v8bf F1[2], F2[2], F3[2];
+                v8h H1[2], H2[2];
+                for (int t = 0; t < 8; t += 2) {
+                    const int pp = t >> 2, k = t & 3;
+                    const float *dp = sm.sD + (4 * pp + g) * FD + (4 * i2 + jc) * 16 + 4 * k;
+                    const v4f d[2] = {*(const v4f *)dp, *(const v4f *)(dp + 4)};
+                    for (int bh = 0; bh < 2; ++bh) {
+                        v2f F;
+                        for (int u = 0; u < 2; ++u) {
+                            F[u] = d[u][0] * Bc[pp][bh][0] + d[u][1] * Bc[pp][bh][1] + d[u][2] * Bc[pp][bh][2] +
+                                   d[u][3] * Bc[pp][bh][3];
+                            // undo the basis scaling and the balance on this operand
+                            if (MODE == 2) F[u] *= fs[pp][k + u > 0];
+                        }
+                        if constexpr (MODE == 1) {
+                            v2bf x1, x2, x3;
+                            split3x2(F, x1, x2, x3);
+                            F1[bh][t] = x1[0]; F1[bh][t + 1] = x1[1];
+                            F2[bh][t] = x2[0]; F2[bh][t + 1] = x2[1];
+                            F3[bh][t] = x3[0]; F3[bh][t + 1] = x3[1];
+                        } else {
+                            v2h x1, x2;
+                            split2hx2(F, x1, x2);
+                            H1[bh][t] = x1[0]; H1[bh][t + 1] = x1[1];
+                            H2[bh][t] = x2[0]; H2[bh][t + 1] = x2[1];
+                        }
+                    }
+                }
+                for (int bh = 0; bh < 2; ++bh) {
+                    v4f c = acc[2 * hf + i2][bh];
+                    if constexpr (MODE == 1) {
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F1[bh], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F2[bh], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahm, F3[bh], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, F1[bh], c, 0, 0, 0);
+                    } else {
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, H1[bh], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, H2[bh], c, 0, 0, 0);
+                    }
+                    acc[2 * hf + i2][bh] = c;
+                }
+            }
+        }
+        // residual: lanes < 32, (a = lane & 7, i = lane >> 3)
+        if (lane < 32) {
+            for (int p = 0; p < np; ++p) {
+                const v4f b = *(const v4f *)(sm.sB + p * FB + 4 * (lane & 7)),
+                          r = *(const v4f *)(sm.sQ + p * FQ_N + FQ_RC + 4 * (lane >> 3));
+                R += b[0] * r[0] + b[1] * r[1] + b[2] * r[2] + b[3] * r[3];
+            }
+        }
+        en_cur = en_next;
+        __syncthreads();
+    }
+
+    // rows 8..15 carry the second split term: fold them onto rows 0..7. The
+    // halves of the wave trade their halves of two tiles, so that every lane ends
+    // with (rows 4 ((lane / 16) % 2) + r, b = 4 (lane / 32) + bb, j) of each i
+    const int bb = (lane >> 2) & 3, jc = lane & 3;
+    const float unscale = (MODE == 2 && s16 != INT_MAX) ? ldexpf(1.0f, -s16) : 1.0f;
+    const int a0 = 4 * ((lane >> 4) & 1), b = 4 * (lane >> 5) + bb;
+    v4f K[4];
+    for (int i = 0; i < 4; ++i)
+        for (int r = 0; r < 4; ++r) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][0][r]), __float_as_uint(acc[i][1][r]),
+                                                             false, false);
+            K[i][r] = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) * unscale;
+        }
+    if (a.vals) {
+        // atomic scatter: no record; each entry is added into its CSR place
+        // (the summation order is the hardware's)
+        float *vals = (float *)a.vals;
+        const int32_t *mst = a.masters + 8 * (int64_t)e;
+        const uint16_t *kk = a.el_kk + 64 * (int64_t)e;
+        if (mst[b] >= 0)
+            for (int r = 0; r < 4; ++r) {
+                const int ma = mst[a0 + r];
+                if (ma < 0) continue;
+                const int64_t r0 = a.nrow_ptr[ma], deg = a.nrow_ptr[ma + 1] - r0;
+                float *dst = vals + 16 * r0 + 4 * (int64_t)kk[8 * (a0 + r) + b] + jc;
+                for (int i = 0; i < 4; ++i) atomicAdd(dst + 4 * i * deg, K[i][r]);
+            }
+    } else {
+        // record of the work item, block-major (block (a, b) of master slots,
+        // entry 4 i + j)
+        for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < 4; ++i) sm.sOut[((a0 + r) * 8 + b) * 16 + 4 * i + jc] = K[i][r];
+        __syncthreads();
+        v4f *dst = (v4f *)((float *)a.em + (a.slot0 + item) * 1024);
+        for (int t = 0; t < 4; ++t) dst[64 * t + lane] = ((const v4f *)sm.sOut)[64 * t + lane];
+    }
+    // residual record of the work item (entry 4 a + i)
+    if (lane < 32 && a.rrec) a.rrec[(a.slot0 + item) * 32 + 4 * (lane & 7) + (lane >> 3)] = (double)R;
+}
+
 // Waves per SIMD the register allocation aims for. The FP64 matrix kernels fit
 // three (OUT elements: 160 VGPRs; at four they spill, 3.00 -> 3.60 ms per step
 // on the 194k-octant sphere). The FP64 sub-cell items stay at two: they run
 // beside the HBM-bound gather, which needs the other registers for its own
 // waves (two-box step of 1.6M octants 12.30 ms at three, 11.75 ms at two; the
-// sphere, where the items outlast the gather, 3.01 against 3.03 ms).
+// sphere, where the items outlast the gather, 3.01 against 3.03 ms). The mixed
+// kernels have the LDS and the registers for four (FP16x2 sphere step 2.14 ms
+// at three, 2.07 at four).
 #define VMS_ASM_BOUNDS(MODE, SUB) \
-    __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((MODE) == 0 && (SUB) ? 2 : 3, 8)))
+    __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((MODE) == 0 ? ((SUB) ? 2 : 3) : 4, 8)))
 
 // OUT elements (SUB = false) two per workgroup: the second element's data
 // and fields load while the first is assembled
 template <typename T, int MODE, bool SUB>
 __global__ VMS_ASM_BOUNDS(MODE, SUB) void k_asm2(AsmArgs a) {
-    __shared__ std::conditional_t<MODE == 0, Smem64, Smem<T>> sm;
+    __shared__ std::conditional_t<MODE == 0, Smem64, SmemF> sm;
     auto item = [&](int64_t i, const ItemPre *pre) {
         if constexpr (MODE == 0) asm_item64<SUB>(a, i, sm, pre);
-        else asm_item<T, MODE, SUB>(a, i, sm, pre);
+        else asm_item32<MODE, SUB>(a, i, sm, pre);
     };
     if constexpr (SUB) {
         item(blockIdx.x, nullptr);
@@ -929,11 +961,11 @@ __global__ VMS_ASM_BOUNDS(MODE, SUB) void k_asm2(AsmArgs a) {
 // from a device counter until none is left, in the order of the unit list
 // (heaviest first); a unit is a run of OUT elements or of sub-cell work items
 // of one tree. One launch for all units.
-template <typename T, int MODE>
-__global__ VMS_ASM_BOUNDS(MODE, true) void k_asm_batch(const AsmArgs *std_args, const AsmArgs *sub_args,
-                                                 const BatchUnit *units, int64_t n_units,
-                                                 unsigned long long *counter) {
-    __shared__ std::conditional_t<MODE == 0, Smem64, Smem<T>> sm;
+template <int MODE, int WPS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void k_asm_batch(
+    const AsmArgs *std_args, const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
+    unsigned long long *counter) {
+    __shared__ std::conditional_t<MODE == 0, Smem64, SmemF> sm;
     __shared__ int64_t su;
     __shared__ AsmArgs sa;  // the unit's tree, read from LDS where used
     for (;;) {
@@ -952,9 +984,9 @@ __global__ VMS_ASM_BOUNDS(MODE, true) void k_asm_batch(const AsmArgs *std_args, 
                 for (int k = 0; k < U.count; ++k) asm_item64<false>(sa, U.first + k, sm, nullptr);
             }
         } else if (U.sub) {
-            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, true>(sa, U.first + k, sm);
+            for (int k = 0; k < U.count; ++k) asm_item32<MODE, true, (WPS > 2)>(sa, U.first + k, sm, nullptr);
         } else {
-            for (int k = 0; k < U.count; ++k) asm_item<T, MODE, false>(sa, U.first + k, sm);
+            for (int k = 0; k < U.count; ++k) asm_item32<MODE, false, (WPS > 2)>(sa, U.first + k, sm, nullptr);
         }
     }
 }
@@ -965,19 +997,23 @@ __global__ void k_reset_counter(unsigned long long *c) {
 
 void launch_assemble_batch(hipStream_t s, int precision, const AsmArgs *std_args,
                            const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
-                           unsigned long long *counter, int n_groups) {
+                           unsigned long long *counter, int n_groups, int n_cu) {
     hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, counter);
     if (n_units <= 0) return;
     dim3 grid((unsigned)n_groups), block(64);
-    if (precision == 0)
-        hipLaunchKernelGGL((k_asm_batch<double, 0>), grid, block, 0, s, std_args, sub_args, units, n_units,
-                           counter);
-    else if (precision == 1)
-        hipLaunchKernelGGL((k_asm_batch<float, 1>), grid, block, 0, s, std_args, sub_args, units, n_units,
-                           counter);
-    else
-        hipLaunchKernelGGL((k_asm_batch<float, 2>), grid, block, 0, s, std_args, sub_args, units, n_units,
-                           counter);
+    // mixed forms: up to two workgroups per SIMD have 256 registers each and
+    // keep the lane's addresses; more of them run the 128-register build (8
+    // trees of 30k octants, BF16x3: 2.98 against 3.23 ms at 8 workgroups per CU,
+    // 3.35 against 2.55 ms at 16)
+    const bool many = n_groups > 8 * n_cu;
+#define VMS_B(MODE, WPS) \
+    hipLaunchKernelGGL((k_asm_batch<MODE, WPS>), grid, block, 0, s, std_args, sub_args, units, n_units, counter)
+    if (precision == 0) VMS_B(0, 2);
+    else if (precision == 1 && many) VMS_B(1, 4);
+    else if (precision == 1) VMS_B(1, 2);
+    else if (many) VMS_B(2, 4);
+    else VMS_B(2, 2);
+#undef VMS_B
 }
 
 // CSR values from the element-matrix records. A thread takes V consecutive

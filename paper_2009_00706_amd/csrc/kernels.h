@@ -174,11 +174,11 @@ struct BatchUnit {
     int32_t count;
     int32_t pad;
 };
-// one persistent launch of n_groups workgroups over all units, in list order;
+// one persistent launch of n_groups workgroups (GPU of n_cu CUs) over all units, in list order;
 // counter: a device counter (reset by the launch sequence)
 void launch_assemble_batch(hipStream_t s, int precision, const AsmArgs *std_args,
                            const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
-                           unsigned long long *counter, int n_groups);
+                           unsigned long long *counter, int n_groups, int n_cu);
 void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu = 0);
 // resident workgroups per CU of the sub-cell item kernel of a precision form
 // (0 FP64, 1 BF16x3, 2 FP16x2; with the matrix), from its registers and LDS
