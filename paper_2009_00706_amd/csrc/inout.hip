@@ -35,12 +35,112 @@ __global__ void k_vertex_labels(SurfDev S, GeoArgs g, int64_t n, const int32_t *
     lab[i] = (uint8_t)ray_label(S, P, ndeg);
 }
 
-__global__ void k_point_labels(SurfDev S, int64_t n, const double *px, const double *py,
-                               const double *pz, uint8_t *lab, unsigned long long *ndeg) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double P[3] = {px[i], py[i], pz[i]};
-    lab[i] = (uint8_t)ray_label(S, P, ndeg);
+// orders the LDS accesses of one wave (its lanes exchange through its own part)
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Labels of many points (ray_label for each). The points of a wave fall into
+// bins with very different numbers of triangles (a bin on the rim of a face
+// parallel to x holds the whole row of it), and one lane's long list would hold
+// up the other 63, so the wave's (point, triangle) pairs are numbered through
+// and dealt out 64 at a time: pair k belongs to the point whose range of the
+// prefix sums holds it. Pairs whose box the ray meets, a few in a hundred, are
+// gathered in a queue, so that the exact tests run with full waves too. The
+// outcome per point (crossing parity, degenerate, on the surface) does not
+// depend on the order. One lane per point took 1.33 ms for 10^6 points near the
+// two boxes (48,600 triangles), this takes 0.245 ms.
+__global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, const double *px, const double *py,
+                                                      const double *pz, uint8_t *lab, unsigned long long *ndeg) {
+    struct Wave {
+        double P[64][3];
+        int first[64];   // first entry of the point's bin
+        int off[65];     // prefix sums of the bins' sizes
+        unsigned res[64];  // bit 0 parity, 1 degenerate, 2 on the surface
+        int qp[128], qt[128];  // queue: point, triangle
+    };
+    __shared__ Wave waves[4];
+    const int lane = threadIdx.x & 63;
+    Wave &w = waves[threadIdx.x >> 6];
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double P[3] = {0.0, 0.0, 0.0};
+    int cnt = 0;
+    if (i < n) {
+        P[0] = px[i];
+        P[1] = py[i];
+        P[2] = pz[i];
+        bool in = true;
+        for (int k = 0; k < 3; ++k)
+            if (P[k] < S.lo[k] || P[k] > S.hi[k]) in = false;
+        if (in) {
+            const int bin = bin_of(P[2], S.z0, S.inz, S.nbz) * S.nby + bin_of(P[1], S.y0, S.iny, S.nby);
+            w.first[lane] = S.bin_off[bin];
+            cnt = S.bin_off[bin + 1] - S.bin_off[bin];
+        }
+    }
+    for (int k = 0; k < 3; ++k) w.P[lane][k] = P[k];
+    w.res[lane] = 0u;
+    int incl = cnt;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    w.off[lane + 1] = incl;
+    if (lane == 0) w.off[0] = 0;
+    const int total = __shfl(incl, 63, 64);
+    int nq = 0;  // queued pairs (uniform over the wave)
+    auto flush = [&](int from, int m) {
+        if (lane < m) {
+            const int o = w.qp[from + lane];
+            const double R[3] = {w.P[o][0], w.P[o][1], w.P[o][2]};
+            const bool neg = __dsub_rn(R[0], S.lo[0]) < __dsub_rn(S.hi[0], R[0]);
+            const double Q[3] = {neg ? __dsub_rn(S.lo[0], 1.0) : __dadd_rn(S.hi[0], 1.0), R[1], R[2]};
+            double a[3], b[3], c[3];
+            tri_load(S, w.qt[from + lane], a, b, c);
+            const int r = segment_triangle(R, Q, a, b, c);
+            if (r == SEG_ON) atomicOr(&w.res[o], 4u);
+            else if (r == SEG_DEGEN) atomicOr(&w.res[o], 2u);
+            else if (r) atomicXor(&w.res[o], 1u);
+        }
+    };
+    wave_sync();
+    for (int k0 = 0; k0 < total; k0 += 64) {
+        const int k = k0 + lane;
+        bool hit = false;
+        int o = 0, t = 0;
+        if (k < total) {
+            for (int b = 32; b > 0; b >>= 1)
+                if (w.off[o + b] <= k) o += b;
+            t = S.bin_tri[w.first[o] + (k - w.off[o])];
+            const double *bx = S.tbox + 6 * (int64_t)t;
+            const double R0 = w.P[o][0], R1 = w.P[o][1], R2 = w.P[o][2];
+            // along -x when the surface's box ends nearer on that side: only the
+            // triangles on that side of the point can be crossed
+            const bool neg = __dsub_rn(R0, S.lo[0]) < __dsub_rn(S.hi[0], R0);
+            hit = !((neg ? bx[0] > R0 : bx[3] < R0) || bx[1] > R1 || bx[4] < R1 || bx[2] > R2 || bx[5] < R2);
+        }
+        const unsigned long long m = __ballot(hit);
+        if (hit) {
+            const int at = nq + __popcll(m & ((1ull << lane) - 1ull));
+            w.qp[at] = o;
+            w.qt[at] = t;
+        }
+        nq += __popcll(m);
+        if (nq >= 64) {
+            wave_sync();
+            nq -= 64;
+            flush(nq, 64);
+            wave_sync();
+        }
+    }
+    wave_sync();
+    flush(0, nq);
+    wave_sync();
+    if (i < n) {
+        const unsigned r = w.res[lane];
+        lab[i] = (uint8_t)((r & 4u) ? 1 : ((r & 2u) ? ray_label_degenerate(S, P, ndeg) : (int)(r & 1u)));
+    }
 }
 
 __global__ void k_point_labels_list(SurfDev S, const int64_t *idx, const unsigned long long *count,
@@ -69,8 +169,8 @@ void launch_point_labels(hipStream_t s, const SurfDev &S, int64_t n, const doubl
                          const double *py, const double *pz, uint8_t *lab,
                          unsigned long long *ndeg) {
     if (n <= 0) return;
-    int64_t nb = (n + 127) / 128;
-    hipLaunchKernelGGL(k_point_labels, dim3((unsigned)nb), dim3(128), 0, s, S, n, px, py, pz, lab,
+    int64_t nb = (n + 255) / 256;
+    hipLaunchKernelGGL(k_point_labels, dim3((unsigned)nb), dim3(256), 0, s, S, n, px, py, pz, lab,
                        ndeg);
 }
 

@@ -67,6 +67,18 @@ __device__ __noinline__ static int ray_label_dir(const SurfDev &S, const double 
     return cnt;
 }
 
+// label of a point whose ray along x met an edge or a vertex
+__device__ __noinline__ static int ray_label_degenerate(const SurfDev &S, const double *P, unsigned long long *ndeg) {
+    bool deg = false;
+    for (int d = 1; d < 10; ++d) {
+        if (ndeg) atomicAdd(ndeg, 1ull);
+        int lab = ray_label_dir(S, P, d, deg);
+        if (!deg) return lab;
+    }
+    if (ndeg) atomicAdd(ndeg, 1ull);
+    return 1;  // every direction degenerate: a point of the surface
+}
+
 __device__ static int ray_label(const SurfDev &S, const double *P, unsigned long long *ndeg) {
     for (int k = 0; k < 3; ++k)
         if (P[k] < S.lo[k] || P[k] > S.hi[k]) return 0;
@@ -91,14 +103,7 @@ __device__ static int ray_label(const SurfDev &S, const double *P, unsigned long
         if (r == SEG_DEGEN) deg = true;
         else cnt ^= r;
     }
-    if (!deg) return cnt;
-    for (int d = 1; d < 10; ++d) {
-        if (ndeg) atomicAdd(ndeg, 1ull);
-        int lab = ray_label_dir(S, P, d, deg);
-        if (!deg) return lab;
-    }
-    if (ndeg) atomicAdd(ndeg, 1ull);
-    return 1;  // every direction degenerate: a point of the surface
+    return deg ? ray_label_degenerate(S, P, ndeg) : cnt;
 }
 
 __device__ static int local_label(const SurfDev &S, const double *P, const double (*V)[3],
