@@ -159,9 +159,14 @@ struct Smem64 {
     double sI[8 * 21];  // per point: u_theta and gradient (4 each), p and gradient, rate (3)
     double sQ[8 * PQ_N];
 };
+// sub-cell items: reference coordinates and weights of 64 points
+struct Smem64Sub : Smem64 {
+    double sX[64][4];
+};
 
 template <bool SUB>
-__device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item, Smem64 &sm, const ItemPre *pre) {
+__device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item, std::conditional_t<SUB, Smem64Sub, Smem64> &sm,
+                                           const ItemPre *pre) {
     const int lane = threadIdx.x;
     __syncthreads();  // the previous item of this workgroup is done with the LDS
     const int e = pre ? pre->e : a.items[item];
@@ -220,41 +225,72 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
     // the residual is one more MFMA whose blocks 0 and 1 are the two halves of
     // the rows a (columns i carry r^i[k]): lane l holds R[4 ((l / 4) % 4) + l / 16][l % 4]
     double accr = 0.0;
-    // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
     const int p8 = lane >> 3, s8 = lane & 7;
+    // the lane's sub-cell entry, loaded 64 points ahead
     const int64_t eoff = SUB ? a.pt_off[item] : 0;
-    uint32_t en_cur = (SUB && p8 < npts) ? a.entries[eoff + p8] : 0u;
+    uint32_t en_cur = (SUB && lane < npts) ? a.entries[eoff + lane] : 0u;
+    if (lane < 8) sm.sB[lane * LB + 32] = 0.0;  // the zero that idle blocks of the residual read
+    const int r_at = i4 < 2 ? c4 * 8 + 4 * i4 + r4 : 32;
     __syncthreads();
 
     for (int base = 0; base < npts; base += 8) {
         const int np = min(8, npts - base);
-        const int pn = base + 8 + p8;
-        const uint32_t en_next = (SUB && pn < npts) ? a.entries[eoff + pn] : 0u;
-        // ---- phase 1: constrained basis at the chunk's points (lane = (p, s));
-        // points beyond the item's last have weight 0
+        if constexpr (SUB) {
+            // decoded 64 points at a time, one per lane (8 lanes per point would
+            // decode each point 8 times)
+            if ((base & 63) == 0) {
+                double xi[3], w;
+                point_xw<true>(a, en_cur, 0, h, xi, w);
+                if (base + lane >= npts) w = 0.0;  // points beyond the item's last weigh nothing
+                for (int k = 0; k < 3; ++k) sm.sX[lane][k] = xi[k];
+                sm.sX[lane][3] = w;
+                const int pn = base + 64 + lane;
+                en_cur = pn < npts ? a.entries[eoff + pn] : 0u;
+                __syncthreads();
+            }
+        }
+        // ---- phase 1: constrained basis at the chunk's points (lane = (p, s))
         double w;
         {
-            double xi[3], b[4] = {0.0, 0.0, 0.0, 0.0};
-            point_xw<SUB>(a, en_cur, SUB ? 0 : p8, h, xi, w);
-            if (SUB && p8 >= np) w = 0.0;
+            double xi[3], b[4];
+            if constexpr (SUB) {
+                const double *X = sm.sX[(base & 63) + p8];
+                for (int k = 0; k < 3; ++k) xi[k] = X[k];
+                w = X[3];
+            } else {
+                point_xw<false>(a, 0u, p8, h, xi, w);
+            }
             const double hg = 0.5 * two_over_h;
-            // vertex v of the constrained slot s: v = s without hanging
-            // corners, else every v with C[v][s] != 0
-            const int v0 = hang ? 0 : s8, v1 = hang ? 8 : s8 + 1;
-#pragma unroll 1
-            for (int v = v0; v < v1; ++v) {
-                const double c = hang ? sm.sC[v * 8 + s8] : 1.0;
-                if (c == 0.0) continue;
+            if (!hang) {
+                // slot s is corner s
                 double f[3], g[3];
                 for (int k = 0; k < 3; ++k) {
-                    const bool up = (v >> k) & 1;
-                    f[k] = 0.5 * (up ? 1.0 + xi[k] : 1.0 - xi[k]);
+                    const bool up = (s8 >> k) & 1;
+                    f[k] = 0.5 + (up ? 0.5 : -0.5) * xi[k];
                     g[k] = up ? hg : -hg;
                 }
-                b[0] += c * (f[0] * f[1] * f[2]);
-                b[1] += c * (g[0] * f[1] * f[2]);
-                b[2] += c * (f[0] * g[1] * f[2]);
-                b[3] += c * (f[0] * f[1] * g[2]);
+                b[0] = f[0] * f[1] * f[2];
+                b[1] = g[0] * f[1] * f[2];
+                b[2] = f[0] * g[1] * f[2];
+                b[3] = f[0] * f[1] * g[2];
+            } else {
+                // every corner v with C[v][s] != 0
+                for (int k = 0; k < 4; ++k) b[k] = 0.0;
+#pragma unroll 1
+                for (int v = 0; v < 8; ++v) {
+                    const double c = sm.sC[v * 8 + s8];
+                    if (c == 0.0) continue;
+                    double f[3], g[3];
+                    for (int k = 0; k < 3; ++k) {
+                        const bool up = (v >> k) & 1;
+                        f[k] = 0.5 * (up ? 1.0 + xi[k] : 1.0 - xi[k]);
+                        g[k] = up ? hg : -hg;
+                    }
+                    b[0] += c * (f[0] * f[1] * f[2]);
+                    b[1] += c * (g[0] * f[1] * f[2]);
+                    b[2] += c * (f[0] * g[1] * f[2]);
+                    b[3] += c * (f[0] * f[1] * g[2]);
+                }
             }
             for (int k = 0; k < 4; ++k) sm.sB[p8 * LB + k * 8 + s8] = b[k];
         }
@@ -347,7 +383,7 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
             const double al = q[PQ_AUP + 2 * c4], ul = q[PQ_AUP + 2 * c4 + 1];
             const double ci = q[PQ_CUP + 2 * i4], ui = q[PQ_CUP + 2 * i4 + 1];
             const double T3 = q[PQ_T3 + r4], W = q[PQ_W], gl = q[gl_at];
-            const double Ar = i4 == 0 ? A0 : (i4 == 1 ? A1 : 0.0);
+            const double Ar = sm.sB[p * LB + r_at];
             accr = __builtin_amdgcn_mfma_f64_4x4x4f64(Ar, q[PQ_RC + 4 * r4 + c4], accr, 0, 0, 0);
             const double a1 = al * T2 + z0 * T1;
             const double bk = al * ci - z0 * ui + kil * W;
@@ -367,7 +403,6 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
                     acc[1][bh][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(A1, F[j][bh], acc[1][bh][j], 0, 0, 0);
                 }
         }
-        en_cur = en_next;
         __syncthreads();
     }
 
@@ -449,6 +484,10 @@ struct SmemF {
     };
     float sSc[8];  // fp16 form: per-point bound of the contraction operands
 };
+// sub-cell items: reference coordinates and weights of 64 points
+struct SmemFSub : SmemF {
+    __attribute__((aligned(16))) float sX[64][4];
+};
 
 // One 4x4 D block, weight folded in (dblock_mv and dblock_simple of vms_point.h
 // on the packed table).
@@ -518,7 +557,8 @@ __device__ inline void dblock_f(const float *q, int i, int j, float rho, float m
 // TIGHT: the lane's addresses and masks are formed anew for every chunk; kept
 // over the loop they take the sub-cell items from 126 VGPRs to over 160
 template <int MODE, bool SUB, bool TIGHT = SUB>
-__device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item, SmemF &sm, const ItemPre *pre) {
+__device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item, std::conditional_t<SUB, SmemFSub, SmemF> &sm,
+                                           const ItemPre *pre) {
     const int lane = threadIdx.x;
     __syncthreads();  // the previous item of this workgroup is done with the LDS
     const int e = pre ? pre->e : a.items[item];
@@ -556,49 +596,78 @@ __device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item,
     v4f acc[4][2];
     for (int t = 0; t < 8; ++t) acc[t >> 1][t & 1] = v4f{0, 0, 0, 0};
     float R = 0.f;  // lanes < 32: residual of (a = lane & 7, i = lane >> 3)
-    // sub-cell entry of the lane's point (lane = (p, s)), loaded one chunk ahead
+    // the lane's sub-cell entry, loaded 64 points ahead
     const int64_t eoff = SUB ? a.pt_off[item] : 0;
-    uint32_t en_cur = (SUB && (lane >> 3) < npts) ? a.entries[eoff + (lane >> 3)] : 0u;
+    uint32_t en_cur = (SUB && lane < npts) ? a.entries[eoff + lane] : 0u;
     __syncthreads();
 
     for (int base = 0; base < npts; base += 8) {
         const int np = min(8, npts - base);
         int lane = threadIdx.x;
         if (TIGHT) asm volatile("" : "+v"(lane));
-        const int pn = base + 8 + (lane >> 3);
-        const uint32_t en_next = (SUB && pn < npts) ? a.entries[eoff + pn] : 0u;
+        if constexpr (SUB) {
+            // decoded 64 points at a time, one per lane (8 lanes per point would
+            // decode each point 8 times)
+            if ((base & 63) == 0) {
+                double xi[3], w;
+                point_xw<true>(a, en_cur, 0, hd, xi, w);
+                *(v4f *)sm.sX[lane] = v4f{(float)xi[0], (float)xi[1], (float)xi[2], (float)w};
+                const int pn = base + 64 + lane;
+                en_cur = pn < npts ? a.entries[eoff + pn] : 0u;
+                __syncthreads();
+            }
+        }
         // ---- phase 1: constrained basis at the chunk's points (lane = (p, s))
         {
             const int p = lane >> 3, s = lane & 7;
-            float b[4] = {0.f, 0.f, 0.f, 0.f};
-            double w = 0.0;
+            float b[4] = {0.f, 0.f, 0.f, 0.f}, w = 0.f;
             if (p < np) {
-                double xi[3];
-                point_xw<SUB>(a, en_cur, base + p, hd, xi, w);
-                // vertex v of the constrained slot s: v = s without hanging
-                // corners, else every v with C[v][s] != 0
-                const float xt[3] = {(float)xi[0], (float)xi[1], (float)xi[2]};
+                float xt[3];
+                if constexpr (SUB) {
+                    const v4f X = *(const v4f *)sm.sX[(base & 63) + p];
+                    for (int k = 0; k < 3; ++k) xt[k] = X[k];
+                    w = X[3];
+                } else {
+                    double xi[3], wd;
+                    point_xw<false>(a, 0u, p, hd, xi, wd);
+                    for (int k = 0; k < 3; ++k) xt[k] = (float)xi[k];
+                    w = (float)wd;
+                }
                 const float hg = 0.5f * (float)two_over_h;
-                const int v0 = hang ? 0 : s, v1 = hang ? 8 : s + 1;
-#pragma unroll 1
-                for (int v = v0; v < v1; ++v) {
-                    const float c = hang ? sm.sC[v * 8 + s] : 1.f;
-                    if (c == 0.f) continue;
+                if (!hang) {
+                    // slot s is corner s
                     float f[3], g[3];
                     for (int k = 0; k < 3; ++k) {
-                        const bool up = (v >> k) & 1;
+                        const bool up = (s >> k) & 1;
                         f[k] = 0.5f * (up ? 1.f + xt[k] : 1.f - xt[k]);
                         g[k] = up ? hg : -hg;
                     }
-                    b[0] += c * (f[0] * f[1] * f[2]);
-                    b[1] += c * (g[0] * f[1] * f[2]);
-                    b[2] += c * (f[0] * g[1] * f[2]);
-                    b[3] += c * (f[0] * f[1] * g[2]);
+                    b[0] = f[0] * f[1] * f[2];
+                    b[1] = g[0] * f[1] * f[2];
+                    b[2] = f[0] * g[1] * f[2];
+                    b[3] = f[0] * f[1] * g[2];
+                } else {
+                    // every corner v with C[v][s] != 0
+#pragma unroll 1
+                    for (int v = 0; v < 8; ++v) {
+                        const float c = sm.sC[v * 8 + s];
+                        if (c == 0.f) continue;
+                        float f[3], g[3];
+                        for (int k = 0; k < 3; ++k) {
+                            const bool up = (v >> k) & 1;
+                            f[k] = 0.5f * (up ? 1.f + xt[k] : 1.f - xt[k]);
+                            g[k] = up ? hg : -hg;
+                        }
+                        b[0] += c * (f[0] * f[1] * f[2]);
+                        b[1] += c * (g[0] * f[1] * f[2]);
+                        b[2] += c * (f[0] * g[1] * f[2]);
+                        b[3] += c * (f[0] * f[1] * g[2]);
+                    }
                 }
             }
             *(v4f *)(sm.sB + p * FB + 4 * s) = v4f{b[0], b[1], b[2], b[3]};
             if (s == 0) {
-                sm.sQ[p * FQ_N + FQ_UT + 3] = (float)w;
+                sm.sQ[p * FQ_N + FQ_UT + 3] = w;
                 if (MODE == 2) sm.sSc[p] = 0.f;
             }
         }
@@ -881,7 +950,6 @@ __device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item,
                 R += b[0] * r[0] + b[1] * r[1] + b[2] * r[2] + b[3] * r[3];
             }
         }
-        en_cur = en_next;
         __syncthreads();
     }
 
@@ -940,7 +1008,8 @@ __device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item,
 // and fields load while the first is assembled
 template <typename T, int MODE, bool SUB>
 __global__ VMS_ASM_BOUNDS(MODE, SUB) void k_asm2(AsmArgs a) {
-    __shared__ std::conditional_t<MODE == 0, Smem64, SmemF> sm;
+    __shared__ std::conditional_t<MODE == 0, std::conditional_t<SUB, Smem64Sub, Smem64>,
+                                  std::conditional_t<SUB, SmemFSub, SmemF>> sm;
     auto item = [&](int64_t i, const ItemPre *pre) {
         if constexpr (MODE == 0) asm_item64<SUB>(a, i, sm, pre);
         else asm_item32<MODE, SUB>(a, i, sm, pre);
@@ -965,7 +1034,7 @@ template <int MODE, int WPS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void k_asm_batch(
     const AsmArgs *std_args, const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
     unsigned long long *counter) {
-    __shared__ std::conditional_t<MODE == 0, Smem64, SmemF> sm;
+    __shared__ std::conditional_t<MODE == 0, Smem64Sub, SmemFSub> sm;
     __shared__ int64_t su;
     __shared__ AsmArgs sa;  // the unit's tree, read from LDS where used
     for (;;) {
