@@ -183,12 +183,12 @@ __device__ __noinline__ bool coplanar_in_triangle(const double *P, const double 
 
 enum { SEG_MISS = 0, SEG_CROSS = 1, SEG_DEGEN = 2, SEG_ON = 3 };
 
-// Segment P -> Q against triangle abc (exact).
+// Segment P -> Q against triangle abc (exact), sq = the sign of Q
+// (orient3d(a, b, c, Q)), which callers with few end points Q keep.
 __device__ inline int segment_triangle(const double *P, const double *Q, const double *a,
-                                       const double *b, const double *c) {
+                                       const double *b, const double *c, int sq) {
     int sp = orient3d(a, b, c, P);
     if (sp == 0) return coplanar_in_triangle(P, a, b, c) ? SEG_ON : SEG_MISS;
-    int sq = orient3d(a, b, c, Q);
     if (sq == 0) return SEG_DEGEN;
     if (sp == sq) return SEG_MISS;
     int e1 = orient3d(P, Q, a, b);
@@ -199,6 +199,10 @@ __device__ inline int segment_triangle(const double *P, const double *Q, const d
     if (np == 3 || nn == 3) return SEG_CROSS;
     if (np && nn) return SEG_MISS;
     return SEG_DEGEN;
+}
+__device__ inline int segment_triangle(const double *P, const double *Q, const double *a,
+                                       const double *b, const double *c) {
+    return segment_triangle(P, Q, a, b, c, orient3d(a, b, c, Q));
 }
 
 }  // namespace vmsd
