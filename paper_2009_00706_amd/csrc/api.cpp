@@ -354,6 +354,9 @@ struct vms_ctx {
     double *d_gm_part = nullptr, *d_gm_h = nullptr, *d_gm_dinv = nullptr;
     int32_t *d_diag_pos = nullptr;
     int *d_gm_bad = nullptr;
+    double *gm_host = nullptr;  // sums the host reads (host memory the device writes), two sets of gm_hset
+    size_t gm_hset = 0;
+    hipEvent_t gm_ev[2] = {};
     // element-matrix records (one per work item: OUT elements first, then the
     // sub-cell items) and, per CSR block, the list of record blocks summed into it
     int64_t n_slots = 0, n_blocks = 0;
@@ -990,6 +993,9 @@ void vms_destroy(vms_ctx *ctx) {
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t &e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
+    for (hipEvent_t e : ctx->gm_ev)
+        if (e) (void)hipEventDestroy(e);
+    if (ctx->gm_host) (void)hipHostFree(ctx->gm_host);
     delete ctx;
 }
 
@@ -1698,7 +1704,8 @@ int vms_dirichlet_in_nodes(vms_ctx *c, void *csr_vals, double *resid) {
 // Gram-Schmidt and one reorthogonalisation pass; Givens rotations and the small
 // triangular solve on the host). A = the assembled matrix, or the matrix-free
 // Jacobian action at the given fields. Inner products are deterministic
-// two-stage sums; every scalar decision is taken on the host in FP64.
+// two-stage sums; decisions are taken on the host in FP64, once per step, while
+// coefficients that only vector updates need are formed on the device.
 int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const double *b, double *x,
               int method, int restart, int max_iter, double rtol, uint32_t flags, int *iters,
               double *rel_res) {
@@ -1727,8 +1734,8 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
         c->d_gm_V = c->d_gm_part = c->d_gm_h = nullptr;
         c->gm_m = 0;
         if (c->buf.alloc(&c->d_gm_V, (size_t)(m + 1) * n) ||
-            c->buf.alloc(&c->d_gm_part, (size_t)(m + 1) * vmsk::multidot_blocks(n)) ||
-            c->buf.alloc(&c->d_gm_h, (size_t)m + 2))
+            c->buf.alloc(&c->d_gm_part, std::max<size_t>(2048, (size_t)(m + 1) * vmsk::sweep_blocks(n))) ||
+            c->buf.alloc(&c->d_gm_h, 2 * ((size_t)m + 2)))
             return fail(c, VMS_ENOMEM, "device allocation failed (Krylov vectors)");
         c->gm_m = m;
     }
@@ -1767,14 +1774,38 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
         return VMS_OK;
     };
     auto prec = [&](const double *in, double *out) { vmsk::launch_bjac_apply(st, c->d_gm_dinv, in, out, N); };
-    // host copies of nk inner products Vb_k . v (the coefficients stay in dh)
-    std::vector<double> hv(m + 2);
-    auto dots = [&](const double *Vb, int nk, const double *v) -> int {
-        vmsk::launch_multidot(st, Vb, n, nk, v, n, c->d_gm_part, dh);
-        HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipMemcpyAsync(hv.data(), dh, sizeof(double) * nk, hipMemcpyDeviceToHost, st));
+    // Sums that the host needs are written into host memory by the kernel that
+    // forms them; two sets, so that one is read while the next is formed. An
+    // event per set tells when it is there.
+    const size_t hset = 2 * ((size_t)m + 2);
+    if (c->gm_hset < hset) {
         HIPCHK(c, hipStreamSynchronize(st));
+        if (c->gm_host) (void)hipHostFree(c->gm_host);
+        c->gm_host = nullptr;
+        c->gm_hset = 0;
+        if (hipHostMalloc((void **)&c->gm_host, 2 * hset * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+            c->gm_host = nullptr;
+            return fail(c, VMS_ENOMEM, "host allocation failed (Krylov coefficients)");
+        }
+        c->gm_hset = hset;
+    }
+    for (hipEvent_t &e : c->gm_ev)
+        if (!e) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    double *hv = c->gm_host;
+    auto ready = [&](int set) -> int {  // to be waited for with hipEventSynchronize
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipEventRecord(c->gm_ev[set], st));
         return VMS_OK;
+    };
+    auto wait = [&](int set) -> int {
+        HIPCHK(c, hipEventSynchronize(c->gm_ev[set]));
+        return VMS_OK;
+    };
+    // nk (1 or 2) inner products Vb_k . v, on the device in dh and on the host in hv
+    auto dots = [&](const double *Vb, int nk, const double *v) -> int {
+        vmsk::launch_dots(st, Vb, n, nk, v, n, c->d_gm_part, dh, hv, 0);
+        int e = ready(0);
+        return e ? e : wait(0);
     };
     int rc;
     if ((rc = dots(b, 1, b))) return rc;
@@ -1806,40 +1837,29 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
             // same multi-dot as the end-of-step residual norm (r and rh adjacent)
             double rho_next = hv[0];
             const int it0 = it;
+            // one wait per step: alpha and omega are formed on the device from the
+            // sums it holds (dh: rh . v, s . s, s . t, t . t, r . r, rh . r); where
+            // the step ends early (rh . v = 0, |s| small, t = 0) its omega is 0
+            const double tol = rtol * bnorm;
             for (int k = 0; it < max_iter; ++k) {
                 const double rho = rho_next;
                 if (rho == 0.0) break;
-                if (k == 0) {
-                    vmsk::launch_axpby(st, 1.0, rr, 0.0, rr, pp, n);
-                } else {
-                    const double beta = (rho / rho_old) * (alpha / omega);
-                    vmsk::launch_axpbypcz(st, 1.0, rr, beta, pp, -beta * omega, vv, pp, n);
-                }
-                prec(pp, ph);
+                vmsk::launch_bcgs_p(st, k == 0, k ? (rho / rho_old) * (alpha / omega) : 0.0, omega, rr, vv,
+                                    c->d_gm_dinv, pp, ph, N);
                 if ((rc = op(ph, vv))) return rc;
-                if ((rc = dots(rh, 1, vv))) return rc;
+                vmsk::launch_dots(st, rh, n, 1, vv, n, c->d_gm_part, dh, nullptr, 0);
+                vmsk::launch_bcgs_s(st, rho, dh, rr, vv, c->d_gm_dinv, ss, sh, N, c->d_gm_part, dh + 1);
+                if ((rc = op(sh, tt))) return rc;
+                vmsk::launch_dots(st, ss, n, 2, tt, n, c->d_gm_part, dh + 2, nullptr, 0);
+                vmsk::launch_bcgs_x(st, rho, tol, dh, ph, sh, ss, tt, rh, x, rr, n, c->d_gm_part, dh + 4, hv, 4);
+                if ((rc = ready(0)) || (rc = wait(0))) return rc;
                 if (hv[0] == 0.0) break;
                 alpha = rho / hv[0];
-                vmsk::launch_axpby(st, 1.0, rr, -alpha, vv, ss, n);
                 ++it;
-                if ((rc = dots(ss, 1, ss))) return rc;
-                if (std::sqrt(hv[0]) <= rtol * bnorm) {  // confirmed by the true residual
-                    vmsk::launch_axpby(st, 1.0, x, alpha, ph, x, n);
-                    break;
-                }
-                prec(ss, sh);
-                if ((rc = op(sh, tt))) return rc;
-                if ((rc = dots(ss, 2, tt))) return rc;  // s.t, t.t
-                if (hv[1] == 0.0) {
-                    vmsk::launch_axpby(st, 1.0, x, alpha, ph, x, n);
-                    break;
-                }
-                omega = hv[0] / hv[1];
-                vmsk::launch_axpbypcz(st, 1.0, x, alpha, ph, omega, sh, x, n);
-                vmsk::launch_axpby(st, 1.0, ss, -omega, tt, rr, n);
-                if ((rc = dots(rr, 2, rr))) return rc;  // r . r, rh . r
-                if (std::sqrt(hv[0]) <= rtol * bnorm || omega == 0.0) break;
-                rho_next = hv[1];
+                if (std::sqrt(hv[1]) <= tol || hv[3] == 0.0) break;  // confirmed by the true residual
+                omega = hv[2] / hv[3];
+                if (std::sqrt(hv[4]) <= tol || omega == 0.0) break;
+                rho_next = hv[5];
                 rho_old = rho;
             }
             if (it == it0) break;  // breakdown before any step: no progress from a restart
@@ -1856,23 +1876,37 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
             res = beta / bnorm;
             if (res <= rtol || it >= max_iter) break;
             vmsk::launch_axpby(st, 1.0 / beta, r, 0.0, r, V, n);
+            prec(V, z);
             std::fill(g.begin(), g.end(), 0.0);
             g[0] = beta;
-            int j = 0;
+            // column j: w = A M^-1 v_j and two Gram-Schmidt passes against V_0 .. V_j,
+            // the second pass' products taken with the first's subtraction and the
+            // norm with the second's; v_{j+1} and its preconditioned copy follow
+            // on the device, so that the next column can be queued at once
+            auto column = [&](int j) -> int {
+                double *h2 = dh + j + 1, *nw = dh + 2 * j + 2;
+                int e = op(z, w);
+                if (e) return e;
+                vmsk::launch_sweep(st, V, n, j + 1, nullptr, true, w, n, c->d_gm_part, dh, nullptr, 0);
+                vmsk::launch_sweep(st, V, n, j + 1, dh, true, w, n, c->d_gm_part, h2, nullptr, 0);
+                vmsk::launch_sweep(st, V, n, j + 1, h2, false, w, n, c->d_gm_part, nw, hv + (j & 1) * hset,
+                                   2 * j + 2);
+                if (j + 1 < m)
+                    vmsk::launch_next_vector(st, w, nw, c->d_gm_dinv, V + (int64_t)(j + 1) * n, z, N);
+                return ready(j & 1);
+            };
+            int j = 0, queued = 0;
+            double drop = 0.0;  // factor by which the last step reduced the residual
             while (j < m && it < max_iter) {
-                double *vj1 = V + (int64_t)(j + 1) * n;
-                prec(V + (int64_t)j * n, z);
-                if ((rc = op(z, w))) return rc;
-                // two Gram-Schmidt passes against V_0 .. V_j
-                if ((rc = dots(V, j + 1, w))) return rc;
-                for (int i = 0; i <= j; ++i) h[i] = hv[i];
-                vmsk::launch_combine(st, V, n, j + 1, dh, w, n, 0);
-                if ((rc = dots(V, j + 1, w))) return rc;
-                for (int i = 0; i <= j; ++i) h[i] += hv[i];
-                vmsk::launch_combine(st, V, n, j + 1, dh, w, n, 0);
-                if ((rc = dots(w, 1, w))) return rc;
-                const double hn = std::sqrt(hv[0]);
-                if (hn > 0.0) vmsk::launch_axpby(st, 1.0 / hn, w, 0.0, w, vj1, n);
+                // the next column runs while this one's rotations are done here, unless
+                // this one is expected to be the last (at the rate of the step before)
+                const bool ahead = std::fabs(g[j]) * drop > rtol * bnorm && j + 1 < m && it + 1 < max_iter;
+                for (; queued < j + 1 + ahead; ++queued)
+                    if ((rc = column(queued))) return rc;
+                if ((rc = wait(j & 1))) return rc;
+                const double *hs = hv + (j & 1) * hset;
+                for (int i = 0; i <= j; ++i) h[i] = hs[i] + hs[j + 1 + i];
+                const double hn = std::sqrt(hs[2 * j + 2]);
                 // Givens rotations
                 for (int i = 0; i < j; ++i) {
                     const double t = cs[i] * h[i] + sn[i] * h[i + 1];
@@ -1886,6 +1920,7 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
                 for (int i = 0; i <= j; ++i) H[i][j] = h[i];
                 g[j + 1] = -sn[j] * g[j];
                 g[j] = cs[j] * g[j];
+                drop = std::fabs(sn[j]);
                 ++j;
                 ++it;
                 if (std::fabs(g[j]) <= rtol * bnorm || hn == 0.0) break;
@@ -1897,7 +1932,7 @@ int vms_solve(vms_ctx *c, const void *csr_vals, const vms_fields *f, const doubl
                 y[i] = H[i][i] != 0.0 ? sum / H[i][i] : 0.0;
             }
             HIPCHK(c, hipMemcpyAsync(dh, y.data(), sizeof(double) * j, hipMemcpyHostToDevice, st));
-            vmsk::launch_combine(st, V, n, j, dh, w, n, 1);
+            vmsk::launch_combine(st, V, n, j, dh, w, n);
             prec(w, z);
             vmsk::launch_axpby(st, 1.0, x, 1.0, z, x, n);
             HIPCHK(c, hipGetLastError());

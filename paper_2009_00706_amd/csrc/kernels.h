@@ -296,19 +296,36 @@ void launch_bjac_invert_f64(hipStream_t s, const double *vals, const int64_t *nr
 void launch_bjac_invert_f32(hipStream_t s, const float *vals, const int64_t *nrow_ptr,
                             const int32_t *diag_pos, int64_t n_nodes, double *dinv, int *bad);
 void launch_bjac_apply(hipStream_t s, const double *dinv, const double *x, double *y, int64_t n_nodes);
-// out[k] = V_k . w for k < nk (V_k = V + k ldv), deterministic; partial holds
-// nk * multidot_blocks(n) doubles
-int multidot_blocks(int64_t n);
-void launch_multidot(hipStream_t s, const double *V, int64_t ldv, int nk, const double *w, int64_t n,
-                     double *partial, double *out);
-// mode 0: w -= sum_k c[k] V_k; mode 1: w = sum_k c[k] V_k (c: device, nk entries)
-void launch_combine(hipStream_t s, const double *V, int64_t ldv, int nk, const double *c, double *w,
-                    int64_t n, int mode);
+// One sweep over w and V_0 .. V_{nk-1} (V_k = V + k ldv, nk <= 201): with c
+// (device, nk entries) w -= sum_k c[k] V_k; then with dots out[k] = V_k . w for
+// every k, else out[0] = w . w (c needed). Deterministic; partial holds
+// max(nk, 1) * sweep_blocks(n) doubles; out on the device; host (nullable, host
+// memory that the device writes): a copy of out and the `before` entries ahead of it
+int sweep_blocks(int64_t n);
+void launch_sweep(hipStream_t s, const double *V, int64_t ldv, int nk, const double *c, bool dots, double *w, int64_t n,
+                  double *partial, double *out, double *host, int before);
+// out[k] = V_k . w for k < nk (1 or 2); the rest as above
+void launch_dots(hipStream_t s, const double *V, int64_t ldv, int nk, const double *w, int64_t n, double *partial,
+                 double *out, double *host, int before);
+// v = w / sqrt(*norm2) (device), z = blockdiag(dinv) v
+void launch_next_vector(hipStream_t s, const double *w, const double *norm2, const double *dinv, double *v, double *z,
+                        int64_t n_nodes);
+// BiCGStab step: p = r + beta (p - omega v) (first: p = r) and ph = M^-1 p;
+// s = r - alpha v with alpha = rho / dot[0], sh = M^-1 s, out[0] = s . s;
+// x += alpha ph + omega sh, r = s - omega t, out[0..1] = r . r, rh . r with omega
+// = dots[2] / dots[3], 0 where the step ends at x + alpha ph (dots: rh . v, s . s,
+// s . t, t . t; tol: |s| at which it ends). partial: 2048 doubles
+void launch_bcgs_p(hipStream_t s, bool first, double beta, double omega, const double *r, const double *v,
+                   const double *dinv, double *p, double *ph, int64_t n_nodes);
+void launch_bcgs_s(hipStream_t s, double rho, const double *dot, const double *r, const double *v, const double *dinv,
+                   double *sv, double *sh, int64_t n_nodes, double *partial, double *out);
+void launch_bcgs_x(hipStream_t s, double rho, double tol, const double *dots, const double *ph, const double *sh,
+                   const double *sv, const double *t, const double *rh, double *x, double *r, int64_t n,
+                   double *partial, double *out, double *host, int before);
+// w = sum_k c[k] V_k (c: device, nk entries)
+void launch_combine(hipStream_t s, const double *V, int64_t ldv, int nk, const double *c, double *w, int64_t n);
 // out = a x + b y
 void launch_axpby(hipStream_t s, double a, const double *x, double b, const double *y, double *out,
                   int64_t n);
-// out = a x + b y + c z
-void launch_axpbypcz(hipStream_t s, double a, const double *x, double b, const double *y, double c,
-                     const double *z, double *out, int64_t n);
 
 }  // namespace vmsk
