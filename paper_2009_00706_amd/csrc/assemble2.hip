@@ -1110,7 +1110,10 @@ __device__ inline void gather_block(const T *em, const int64_t *cb_off, const in
         for (int u = 0; u < 4; ++u) r[u] = c + u < c1 ? contrib[c + u] : -1;
         vec v[4];
         for (int u = 0; u < 4; ++u)
-            if (r[u] >= 0) v[u] = *(const vec *)(em + (int64_t)r[u] * 16 + e0);
+            if (r[u] >= 0) {
+                const vec *src = (const vec *)(em + (int64_t)r[u] * 16 + e0);
+                v[u] = sizeof(T) == 8 ? __builtin_nontemporal_load(src) : *src;
+            }
         for (int u = 0; u < 4; ++u)
             if (r[u] >= 0)
                 for (int q = 0; q < V; ++q) s[q] += (double)v[u][q];
@@ -1124,11 +1127,20 @@ __device__ inline void gather_block(const T *em, const int64_t *cb_off, const in
     __builtin_nontemporal_store(o, (vec *)dst);
 }
 
+// Bound by HBM (15.6 GB in 3.6 ms for the two-box case of 1.35 M octants in FP64:
+// 4.3 TB/s, the rate of a large copy). Workgroups go round the 8 XCDs in turn; the
+// FP64 gather gives each XCD one contiguous range of blocks instead (its grid is a
+// multiple of 8), so that workgroups which share lines of the block headers and
+// of the CSR rows share an L2, and its records, read once, pass the caches by:
+// 16^3 triquadratic elements 482 -> 456 us, the two-box step 11.22 -> 11.07 ms. FP32
+// records are more often still in the caches, where going round finds them
+// sooner (29k hanging-node octants: 686 us so, 706 us by ranges).
 template <typename T, int V, bool SKIP_LATE>
 __global__ void k_gather(const T *em, const int64_t *cb_off, const int32_t *contrib,
                          const int64_t *vbase, const int32_t *vstride, int64_t nb, T *vals) {
     constexpr int TPB = 16 / V;  // threads per block
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t wg = sizeof(T) == 8 ? (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int64_t g = wg * blockDim.x + threadIdx.x;
     const int64_t B = g / TPB;
     if (B >= nb) return;
     gather_block<T, V, SKIP_LATE>(em, cb_off, contrib, vbase, vstride, B, (int)(g % TPB) * V, vals);
@@ -1231,7 +1243,7 @@ void launch_gather_f64(hipStream_t s, const double *em, const int64_t *cb_off, c
                        const int64_t *vbase, const int32_t *vstride, int64_t nb, double *vals,
                        bool skip_late) {
     if (nb <= 0) return;
-    const dim3 grid((unsigned)((8 * nb + 255) / 256));
+    const dim3 grid((unsigned)((8 * nb + 2047) / 2048 * 8));
     if (skip_late)
         hipLaunchKernelGGL((k_gather<double, 2, true>), grid, dim3(256), 0, s, em, cb_off, contrib, vbase,
                            vstride, nb, vals);
