@@ -1394,26 +1394,30 @@ static int ensure_side(vms_ctx *c) {
 // and sums the late blocks; every block is summed by the same code in the same
 // order either way, so the outputs are identical.
 // Workgroups per CU of the second stream's kernels (exact relabel, sub-cell
-// items) while they run beside the CSR gather in the overlapped schedule. The
-// gather is bound by HBM and needs many waves in flight; the second stream's
-// kernels are latency-bound and lose little when fewer of their waves are
-// resident. When their estimated work fits well inside the gather's (under
-// 0.8 of it), the sub-cell items keep ceil(w/2) of their w waves per SIMD and
-// the relabel a third of its workgroups per CU (the choices that measured
-// best on MI355X); otherwise neither is limited. Estimates from rates measured
-// on this GPU: 0.51 ns per sub-cell point over the whole GPU in FP64, 0.33 ns
-// in the mixed forms, 1.5e10 exact labels per second in the relabel, the
-// gather's bytes (records read, values written) at 4.7 TB/s (FP64 values) or
-// 4.0 TB/s (FP32). 0 = no limit.
+// items) while they run beside the CSR gather in the overlapped schedule; 0 = no
+// limit. Without limits they leave few registers to the gather, which gets less
+// than half of its work done beside them; with half of their waves the sub-cell
+// items take 1.45 (FP64) or 1.25 times (mixed) as long and the gather runs at its
+// full rate; a relabel at a third of its waves takes 2.7 times as long. So
+// the items are limited where that ends sooner, and the relabel too where all of it
+// still fits beside the gather. Measured, no limit / items / both: two boxes of 1.35
+// M octants FP64 10.9 / 9.9 / 11.5 ms, BF16x3 8.0 / 7.2 / 8.7 ms; of 4.7 M octants 33.2
+// / 30.6 / 35.9 and 24.8 / 21.9 / 26.6 ms; of 12 M octants 71.3 / 68.9 / 67.4 and
+// 51.7 / 47.6 / 46.0 ms; sphere (mostly sub-cell points) FP64 2.77 / 3.65 / 4.24 ms.
+// Estimates from rates measured on this GPU: 0.44 ns per sub-cell point over the
+// whole GPU in FP64, 0.31 ns in the mixed forms, 2.0e10 exact labels per second in
+// the relabel, the gather's bytes (records read, values written) at 4.3 TB/s
+// (FP64 values) or 3.75 TB/s (FP32).
 static void side_caps(vms_ctx *c, bool relabel, int &items_cap, int &relabel_cap) {
     items_cap = relabel_cap = 0;
     const bool fp64 = c->prm.precision == VMS_FP64;
     const double vb = fp64 ? 8.0 : 4.0;
-    const double t_items = (double)c->n_subgp * (fp64 ? 0.51e-9 : 0.33e-9);
-    const double t_rel = relabel ? (double)c->n_labelled / 1.5e10 : 0.0;
+    const double t_items = (double)c->n_subgp * (fp64 ? 0.44e-9 : 0.31e-9);
+    const double t_rel = relabel ? (double)c->n_labelled / 2.0e10 : 0.0;
     const double recs = (double)(c->n_std + c->n_sub_items);
-    const double t_gather = (recs * 1024.0 + (double)c->mesh.nnz) * vb / (fp64 ? 4.7e12 : 4.0e12);
-    if (!(t_items + t_rel < 0.8 * t_gather)) return;
+    const double t_gather = (recs * 1024.0 + (double)c->mesh.nnz) * vb / (fp64 ? 4.3e12 : 3.75e12);
+    const double t_free = t_rel + t_items, t_half = (fp64 ? 1.45 : 1.25) * t_items;
+    if (!(std::max(t_rel + t_half, t_gather) < std::max(t_free, t_gather + 0.55 * t_free))) return;
     if (c->sub_cap < 0) {
         const int per_cu = vmsk::sub_items_per_cu(fp64 ? 0 : (c->prm.precision == VMS_MIXED_BF16 ? 1 : 2));
         const int w = per_cu / 4;  // waves per SIMD: one-wave workgroups, 4 SIMDs per CU
@@ -1423,7 +1427,7 @@ static void side_caps(vms_ctx *c, bool relabel, int &items_cap, int &relabel_cap
         c->rel_cap = sq >= 9 ? (sq + 2) / 3 : 0;
     }
     items_cap = c->sub_cap;
-    relabel_cap = relabel ? c->rel_cap : 0;
+    relabel_cap = relabel && 2.7 * t_rel + t_half < t_gather ? c->rel_cap : 0;
 }
 
 static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *resid, uint32_t flags,
