@@ -965,13 +965,17 @@ static void gather_resid(vms_ctx *c, hipStream_t st, double *out) {
 
 // CSR values = sums of the element-matrix records; the identity blocks of
 // inactive nodes are written by the same gather
-static void gather_csr(vms_ctx *c, hipStream_t st, void *vals) {
+// (and, resid not null, the residual in the same launch)
+static vmsk::ResSum res_sum(vms_ctx *c, double *resid) {
+    return {c->d_rrec, c->d_roff, c->d_rlist, c->mesh.n_nodes, resid};
+}
+static void gather_csr(vms_ctx *c, hipStream_t st, void *vals, double *resid) {
     if (c->prm.precision == VMS_FP64)
         vmsk::launch_gather_f64(st, (const double *)c->d_em, c->d_cb_off, c->d_contrib, c->d_vbase,
-                                c->d_vstride, c->n_blocks, (double *)vals);
+                                c->d_vstride, c->n_blocks, (double *)vals, false, res_sum(c, resid));
     else
         vmsk::launch_gather_f32(st, (const float *)c->d_em, c->d_cb_off, c->d_contrib, c->d_vbase,
-                                c->d_vstride, c->n_blocks, (float *)vals);
+                                c->d_vstride, c->n_blocks, (float *)vals, false, res_sum(c, resid));
 }
 
 extern "C" {
@@ -1521,7 +1525,7 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         HIPCHK(c, hipStreamWaitEvent(ms, c->join, 0));
         if (late_rc) return late_rc;
         vmsk::launch_gather_list(ms, fp64, em, c->d_cb_off, c->d_contrib, c->d_vbase, c->d_vstride, c->d_late,
-                                 c->n_late, vals);
+                                 c->n_late, vals, res_sum(c, resid));
     } else {
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[4], ms));
         if (atomic) {
@@ -1533,10 +1537,10 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
                 vmsk::launch_dirichlet_rows_f32(ms, (float *)vals, c->d_nrow_ptr, c->d_diag_pos, c->d_inact,
                                                 c->n_inact, nullptr);
         } else if (mat) {
-            gather_csr(c, ms, vals);
+            gather_csr(c, ms, vals, resid);
         }
+        if (resid && (atomic || !mat)) gather_resid(c, ms, resid);
     }
-    if (resid) gather_resid(c, ms, resid);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[5], ms));
     return VMS_OK;

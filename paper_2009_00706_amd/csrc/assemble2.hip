@@ -1127,6 +1127,36 @@ __device__ inline void gather_block(const T *em, const int64_t *cb_off, const in
     __builtin_nontemporal_store(o, (vec *)dst);
 }
 
+// residual of node n from the residual records (one thread per node, its entries
+// in ascending record order, four in flight)
+__device__ inline void res_node(const double *rrec, const int64_t *roff, const int32_t *rlist, int64_t n,
+                                double *out) {
+    const int64_t c0 = roff[n], c1 = roff[n + 1];
+    v4d s = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t c = c0; c < c1; c += 4) {
+        int32_t q[4];
+        for (int u = 0; u < 4; ++u) q[u] = c + u < c1 ? rlist[c + u] : -1;
+        v4d v[4];
+        for (int u = 0; u < 4; ++u)
+            if (q[u] >= 0) v[u] = *(const v4d *)(rrec + 4 * (int64_t)q[u]);
+        for (int u = 0; u < 4; ++u)
+            if (q[u] >= 0)
+                for (int e = 0; e < 4; ++e) s[e] += v[u][e];
+    }
+    for (int e = 0; e < 4; ++e) out[4 * n + e] = s[e];
+}
+
+// The residual's summation rides in the launch of the CSR blocks' (the first nr
+// workgroups): on small meshes a launch of its own costs as much as the
+// summation (504 octants, FP64: 13.9 us a step, 18.1 us with a second launch).
+__device__ inline bool res_part(const ResSum &r, unsigned nr) {
+    if (blockIdx.x >= nr) return false;
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n < r.n_nodes) res_node(r.rrec, r.roff, r.rlist, n, r.out);
+    return true;
+}
+static unsigned res_groups(const ResSum &r) { return r.out ? (unsigned)((r.n_nodes + 255) / 256) : 0u; }
+
 // Bound by HBM (15.6 GB in 3.6 ms for the two-box case of 1.35 M octants in FP64:
 // 4.3 TB/s, the rate of a large copy). Workgroups go round the 8 XCDs in turn; the
 // FP64 gather gives each XCD one contiguous range of blocks instead (its grid is a
@@ -1137,9 +1167,12 @@ __device__ inline void gather_block(const T *em, const int64_t *cb_off, const in
 // sooner (29k hanging-node octants: 686 us so, 706 us by ranges).
 template <typename T, int V, bool SKIP_LATE>
 __global__ void k_gather(const T *em, const int64_t *cb_off, const int32_t *contrib,
-                         const int64_t *vbase, const int32_t *vstride, int64_t nb, T *vals) {
+                         const int64_t *vbase, const int32_t *vstride, int64_t nb, T *vals, ResSum r, unsigned nr) {
     constexpr int TPB = 16 / V;  // threads per block
-    const int64_t wg = sizeof(T) == 8 ? (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    if constexpr (!SKIP_LATE)
+        if (res_part(r, nr)) return;
+    const unsigned b = blockIdx.x - nr;
+    const int64_t wg = sizeof(T) == 8 ? (int64_t)(b & 7) * ((gridDim.x - nr) >> 3) + (b >> 3) : b;
     const int64_t g = wg * blockDim.x + threadIdx.x;
     const int64_t B = g / TPB;
     if (B >= nb) return;
@@ -1150,9 +1183,10 @@ __global__ void k_gather(const T *em, const int64_t *cb_off, const int32_t *cont
 template <typename T, int V>
 __global__ void k_gather_list(const T *em, const int64_t *cb_off, const int32_t *contrib,
                               const int64_t *vbase, const int32_t *vstride, const int64_t *list, int64_t n,
-                              T *vals) {
+                              T *vals, ResSum r, unsigned nr) {
     constexpr int TPB = 16 / V;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (res_part(r, nr)) return;
+    const int64_t g = (int64_t)(blockIdx.x - nr) * blockDim.x + threadIdx.x;
     const int64_t k = g / TPB;
     if (k >= n) return;
     gather_block<T, V>(em, cb_off, contrib, vbase, vstride, list[k], (int)(g % TPB) * V, vals);
@@ -1172,34 +1206,24 @@ __device__ inline int tree_of(const int64_t *prefix, int n, int64_t g) {
 }
 
 template <typename T, int V>
-__global__ void k_gather_batch(const GatherTab *tabs, const int64_t *prefix, int n_trees) {
+__global__ void k_gather_batch(const GatherTab *tabs, const int64_t *prefix, const int64_t *node_prefix, int n_trees,
+                               unsigned nr) {
     constexpr int TPB = 16 / V;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x < nr) {
+        const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+        if (g >= node_prefix[n_trees]) return;
+        const int t = tree_of(node_prefix, n_trees, g);
+        const GatherTab &G = tabs[t];
+        if (G.resid) res_node(G.rrec, G.roff, G.rlist, g - node_prefix[t], G.resid);
+        return;
+    }
+    const int64_t g = (int64_t)(blockIdx.x - nr) * blockDim.x + threadIdx.x;
     const int64_t Bg = g / TPB;
     if (Bg >= prefix[n_trees]) return;
     const int t = tree_of(prefix, n_trees, Bg);
     const GatherTab &G = tabs[t];
     gather_block<T, V>((const T *)G.em, G.cb_off, G.contrib, G.vbase, G.vstride, Bg - prefix[t],
                        (int)(g % TPB) * V, (T *)G.vals);
-}
-
-// residual by node from the residual records (one thread per node, its
-// entries in ascending record order)
-__device__ inline void res_node(const double *rrec, const int64_t *roff, const int32_t *rlist, int64_t n,
-                                double *out) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int64_t c = roff[n]; c < roff[n + 1]; ++c) {
-        const int64_t q = rlist[c];
-        const v4d v = *(const v4d *)(rrec + (q >> 3) * 32 + 4 * (q & 7));
-        s0 += v[0];
-        s1 += v[1];
-        s2 += v[2];
-        s3 += v[3];
-    }
-    out[4 * n] = s0;
-    out[4 * n + 1] = s1;
-    out[4 * n + 2] = s2;
-    out[4 * n + 3] = s3;
 }
 
 __global__ void k_res_gather(const double *rrec, const int64_t *roff, const int32_t *rlist, int64_t n_nodes,
@@ -1209,27 +1233,18 @@ __global__ void k_res_gather(const double *rrec, const int64_t *roff, const int3
     res_node(rrec, roff, rlist, n, out);
 }
 
-__global__ void k_res_gather_batch(const GatherTab *tabs, const int64_t *prefix, int n_trees) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= prefix[n_trees]) return;
-    const int t = tree_of(prefix, n_trees, g);
-    const GatherTab &G = tabs[t];
-    if (G.resid) res_node(G.rrec, G.roff, G.rlist, g - prefix[t], G.resid);
-}
-
 void launch_gather_batch(hipStream_t s, int precision, const GatherTab *tabs, const int64_t *blk_prefix,
                          int64_t n_blocks, const int64_t *node_prefix, int64_t n_nodes, int n_trees) {
-    if (n_blocks > 0) {
-        if (precision == 0)
-            hipLaunchKernelGGL((k_gather_batch<double, 2>), dim3((unsigned)((8 * n_blocks + 255) / 256)),
-                               dim3(256), 0, s, tabs, blk_prefix, n_trees);
-        else
-            hipLaunchKernelGGL((k_gather_batch<float, 4>), dim3((unsigned)((4 * n_blocks + 255) / 256)),
-                               dim3(256), 0, s, tabs, blk_prefix, n_trees);
-    }
-    if (n_nodes > 0)
-        hipLaunchKernelGGL(k_res_gather_batch, dim3((unsigned)((n_nodes + 255) / 256)), dim3(256), 0, s, tabs,
-                           node_prefix, n_trees);
+    const unsigned nr = (unsigned)((n_nodes + 255) / 256);
+    const int64_t threads = (precision == 0 ? 8 : 4) * n_blocks;
+    const dim3 grid(nr + (unsigned)((threads + 255) / 256));
+    if (grid.x == 0) return;
+    if (precision == 0)
+        hipLaunchKernelGGL((k_gather_batch<double, 2>), grid, dim3(256), 0, s, tabs, blk_prefix, node_prefix, n_trees,
+                           nr);
+    else
+        hipLaunchKernelGGL((k_gather_batch<float, 4>), grid, dim3(256), 0, s, tabs, blk_prefix, node_prefix, n_trees,
+                           nr);
 }
 
 void launch_res_gather(hipStream_t s, const double *rrec, const int64_t *roff, const int32_t *rlist,
@@ -1241,38 +1256,42 @@ void launch_res_gather(hipStream_t s, const double *rrec, const int64_t *roff, c
 
 void launch_gather_f64(hipStream_t s, const double *em, const int64_t *cb_off, const int32_t *contrib,
                        const int64_t *vbase, const int32_t *vstride, int64_t nb, double *vals,
-                       bool skip_late) {
-    if (nb <= 0) return;
-    const dim3 grid((unsigned)((8 * nb + 2047) / 2048 * 8));
+                       bool skip_late, const ResSum &r) {
+    const unsigned nr = skip_late ? 0u : res_groups(r);
+    const dim3 grid(nr + (unsigned)((8 * nb + 2047) / 2048 * 8));
+    if (grid.x == 0) return;
     if (skip_late)
         hipLaunchKernelGGL((k_gather<double, 2, true>), grid, dim3(256), 0, s, em, cb_off, contrib, vbase,
-                           vstride, nb, vals);
+                           vstride, nb, vals, r, nr);
     else
         hipLaunchKernelGGL((k_gather<double, 2, false>), grid, dim3(256), 0, s, em, cb_off, contrib, vbase,
-                           vstride, nb, vals);
+                           vstride, nb, vals, r, nr);
 }
 void launch_gather_f32(hipStream_t s, const float *em, const int64_t *cb_off, const int32_t *contrib,
                        const int64_t *vbase, const int32_t *vstride, int64_t nb, float *vals,
-                       bool skip_late) {
-    if (nb <= 0) return;
-    const dim3 grid((unsigned)((4 * nb + 255) / 256));
+                       bool skip_late, const ResSum &r) {
+    const unsigned nr = skip_late ? 0u : res_groups(r);
+    const dim3 grid(nr + (unsigned)((4 * nb + 255) / 256));
+    if (grid.x == 0) return;
     if (skip_late)
         hipLaunchKernelGGL((k_gather<float, 4, true>), grid, dim3(256), 0, s, em, cb_off, contrib, vbase,
-                           vstride, nb, vals);
+                           vstride, nb, vals, r, nr);
     else
         hipLaunchKernelGGL((k_gather<float, 4, false>), grid, dim3(256), 0, s, em, cb_off, contrib, vbase,
-                           vstride, nb, vals);
+                           vstride, nb, vals, r, nr);
 }
 void launch_gather_list(hipStream_t s, bool fp64, const void *em, const int64_t *cb_off, const int32_t *contrib,
                         const int64_t *vbase, const int32_t *vstride, const int64_t *list, int64_t n,
-                        void *vals) {
-    if (n <= 0) return;
+                        void *vals, const ResSum &r) {
+    const unsigned nr = res_groups(r);
+    const dim3 grid(nr + (unsigned)(((fp64 ? 8 : 4) * n + 255) / 256));
+    if (grid.x == 0) return;
     if (fp64)
-        hipLaunchKernelGGL((k_gather_list<double, 2>), dim3((unsigned)((8 * n + 255) / 256)), dim3(256), 0, s,
-                           (const double *)em, cb_off, contrib, vbase, vstride, list, n, (double *)vals);
+        hipLaunchKernelGGL((k_gather_list<double, 2>), grid, dim3(256), 0, s, (const double *)em, cb_off, contrib,
+                           vbase, vstride, list, n, (double *)vals, r, nr);
     else
-        hipLaunchKernelGGL((k_gather_list<float, 4>), dim3((unsigned)((4 * n + 255) / 256)), dim3(256), 0, s,
-                           (const float *)em, cb_off, contrib, vbase, vstride, list, n, (float *)vals);
+        hipLaunchKernelGGL((k_gather_list<float, 4>), grid, dim3(256), 0, s, (const float *)em, cb_off, contrib,
+                           vbase, vstride, list, n, (float *)vals, r, nr);
 }
 
 // dynamic LDS that holds a kernel to at most wg_per_cu resident workgroups per

@@ -191,16 +191,25 @@ size_t lds_for_cap(const void *kernel, int wg_per_cu);
 // surface items; skip_late leaves those blocks to launch_gather_list, so that
 // the rest can be summed as soon as the OUT-element records exist.
 constexpr int32_t VS_LATE = 1 << 30;
+// The residual's summation, in the same launch (out null: none; not with
+// skip_late): the arguments of launch_res_gather
+struct ResSum {
+    const double *rrec = nullptr;
+    const int64_t *roff = nullptr;
+    const int32_t *rlist = nullptr;
+    int64_t n_nodes = 0;
+    double *out = nullptr;
+};
 void launch_gather_f64(hipStream_t s, const double *em, const int64_t *cb_off, const int32_t *contrib,
                        const int64_t *vbase, const int32_t *vstride, int64_t nb, double *vals,
-                       bool skip_late = false);
+                       bool skip_late = false, const ResSum &r = {});
 void launch_gather_f32(hipStream_t s, const float *em, const int64_t *cb_off, const int32_t *contrib,
                        const int64_t *vbase, const int32_t *vstride, int64_t nb, float *vals,
-                       bool skip_late = false);
+                       bool skip_late = false, const ResSum &r = {});
 // the same for the n listed blocks only (list: DEVICE, block indices)
 void launch_gather_list(hipStream_t s, bool fp64, const void *em, const int64_t *cb_off, const int32_t *contrib,
                         const int64_t *vbase, const int32_t *vstride, const int64_t *list, int64_t n,
-                        void *vals);
+                        void *vals, const ResSum &r = {});
 void launch_fill_f64(hipStream_t s, double *p, int64_t n, double v);
 void launch_fill_f32(hipStream_t s, float *p, int64_t n, float v);
 // Triquadratic (27-node) elements of a uniform octree, FP64: element node
@@ -217,8 +226,6 @@ struct Q2Args {
     double *rrec;
 };
 void launch_q2(hipStream_t s, const Q2Args &a);
-void launch_q2_res_gather(hipStream_t s, const double *rrec, const int64_t *roff, const int32_t *rlist,
-                          int64_t n_nodes, double *out);
 
 // One tree's summation lists and outputs, for the batched gathers.
 struct GatherTab {

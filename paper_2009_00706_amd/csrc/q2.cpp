@@ -277,8 +277,7 @@ int vms_q2_assemble(vms_q2 *q, const vms_fields *f, double *csr_vals, double *re
     vmsk::launch_q2(q->stream, a);
     (void)hipEventRecord(q->ev[1], q->stream);
     vmsk::launch_gather_f64(q->stream, q->d_em, q->d_cb_off, q->d_contrib, q->d_vbase, q->d_vstride,
-                            q->n_blocks, csr_vals);
-    if (resid) vmsk::launch_q2_res_gather(q->stream, q->d_rrec, q->d_roff, q->d_rlist, q->n_nodes, resid);
+                            q->n_blocks, csr_vals, false, {q->d_rrec, q->d_roff, q->d_rlist, q->n_nodes, resid});
     (void)hipEventRecord(q->ev[2], q->stream);
     q->timed = true;
     hipError_t e = hipGetLastError();

@@ -220,31 +220,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-// residual of every node from the element records (its (element, node slot)
-// entries in ascending order)
-__global__ void k_q2_res_gather(const double *rrec, const int64_t *roff, const int32_t *rlist, int64_t n_nodes,
-                                double *out) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= n_nodes) return;
-    double r[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t c = roff[n]; c < roff[n + 1]; ++c) {
-        const int64_t q = rlist[c];
-        for (int k = 0; k < 4; ++k) r[k] += rrec[4 * q + k];
-    }
-    for (int k = 0; k < 4; ++k) out[4 * n + k] = r[k];
-}
-
 void launch_q2(hipStream_t s, const Q2Args &a) {
     if (a.n_el <= 0) return;
     const int64_t n = a.n_el < 512 ? a.n_el : 512;  // two workgroups per CU
     hipLaunchKernelGGL(k_q2, dim3((unsigned)n), dim3(256), 0, s, a);
-}
-
-void launch_q2_res_gather(hipStream_t s, const double *rrec, const int64_t *roff, const int32_t *rlist,
-                          int64_t n_nodes, double *out) {
-    if (n_nodes <= 0) return;
-    hipLaunchKernelGGL(k_q2_res_gather, dim3((unsigned)((n_nodes + 255) / 256)), dim3(256), 0, s, rrec, roff,
-                       rlist, n_nodes, out);
 }
 
 }  // namespace vmsk
