@@ -136,7 +136,11 @@ __device__ inline void load_pre2(const AsmArgs &a, int64_t i0, int64_t i1, bool 
 // blocks evaluated in two divergent passes, written to LDS (17.2 KB per
 // workgroup, 2.25 waves per SIMD) and read back, the OUT elements of the
 // 194k-octant sphere took 0.625 ms and its sub-cell items 2.19 ms; now 0.504 and
-// 1.89 ms with 9.8 KB.
+// 1.65 ms with 9.7 and 20.2 KB. The point tables (a quarter of the sub-cell items'
+// VALU work) take four lanes per point: 16 points at a time fill the wave, in what
+// LDS two waves per SIMD leave (8 at a time: 1.72 ms). An OUT element has only 8
+// points, and those of two elements at once would cost a wave per SIMD; the batch
+// kernel, which serves both, keeps 8 (8 trees of 30k octants: 3.59 ms, 3.85 at 16).
 #define PQ_T12 0   // (T1, T2)[r], pairs
 #define PQ_AUP 8   // (alpha, theta u')[c], pairs
 #define PQ_CUP 16  // (c, u')[i], pairs; i = 3: (tau_M, 0)
@@ -152,21 +156,27 @@ __device__ inline void load_pre2(const AsmArgs &a, int64_t i0, int64_t i1, bool 
 // Fields at the master slots are combined as they are loaded: rows 0-2
 // u_theta, 3 p, 4-6 the rate (u - u_prev) / dt, of which only the value is
 // interpolated.
-struct Smem64 {
+template <int N>
+struct Smem64T {
+    static constexpr int NP = N;  // points tabulated at once
     double sU[7 * LU];
     double sC[64];
-    double sB[8 * LB];
-    double sI[8 * 21];  // per point: u_theta and gradient (4 each), p and gradient, rate (3)
-    double sQ[8 * PQ_N];
+    double sB[NP * LB];
+    double sI[NP * 19];  // per point: u_theta and gradient (4 each), p and gradient, rate (3)
+    double sQ[NP * PQ_N - 1];  // the last row ends without its pad
 };
+// OUT elements: all 8 points
+using Smem64 = Smem64T<8>;
 // sub-cell items: reference coordinates and weights of 64 points
-struct Smem64Sub : Smem64 {
+template <int N>
+struct Smem64Sub : Smem64T<N> {
     double sX[64][4];
 };
 
-template <bool SUB>
-__device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item, std::conditional_t<SUB, Smem64Sub, Smem64> &sm,
+template <bool SUB, typename SM>  // SM: Smem64 or Smem64Sub<8 or 16>
+__device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item, SM &sm,
                                            const ItemPre *pre) {
+    constexpr int NP = SUB ? SM::NP : 8;
     const int lane = threadIdx.x;
     __syncthreads();  // the previous item of this workgroup is done with the LDS
     const int e = pre ? pre->e : a.items[item];
@@ -229,12 +239,12 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
     // the lane's sub-cell entry, loaded 64 points ahead
     const int64_t eoff = SUB ? a.pt_off[item] : 0;
     uint32_t en_cur = (SUB && lane < npts) ? a.entries[eoff + lane] : 0u;
-    if (lane < 8) sm.sB[lane * LB + 32] = 0.0;  // the zero that idle blocks of the residual read
+    if (lane < NP) sm.sB[lane * LB + 32] = 0.0;  // the zero that idle blocks of the residual read
     const int r_at = i4 < 2 ? c4 * 8 + 4 * i4 + r4 : 32;
     __syncthreads();
 
-    for (int base = 0; base < npts; base += 8) {
-        const int np = min(8, npts - base);
+    for (int base = 0; base < npts; base += NP) {
+        const int np = min(NP, npts - base);
         if constexpr (SUB) {
             // decoded 64 points at a time, one per lane (8 lanes per point would
             // decode each point 8 times)
@@ -250,11 +260,22 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
             }
         }
         // ---- phase 1: constrained basis at the chunk's points (lane = (p, s))
-        double w;
-        {
+        double w = 0.0;
+        // the chunk's points, 8 at a time. A loop also where there are only 8: without
+        // it the OUT elements' kernel spills at three waves per SIMD, with it the
+        // batch's loses 1% (its registers suffice either way).
+        auto eights = [&](auto f) {
+            if constexpr (std::is_same_v<SM, Smem64Sub<8>>) {
+                f(p8);
+            } else {
+#pragma unroll 1
+                for (int p = p8; p < NP && p - p8 < np; p += 8) f(p);
+            }
+        };
+        eights([&](int p) {
             double xi[3], b[4];
             if constexpr (SUB) {
-                const double *X = sm.sX[(base & 63) + p8];
+                const double *X = sm.sX[(base & 63) + p];
                 for (int k = 0; k < 3; ++k) xi[k] = X[k];
                 w = X[3];
             } else {
@@ -292,32 +313,35 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
                     b[3] += c * (f[0] * f[1] * g[2]);
                 }
             }
-            for (int k = 0; k < 4; ++k) sm.sB[p8 * LB + k * 8 + s8] = b[k];
-        }
+            for (int k = 0; k < 4; ++k) sm.sB[p * LB + k * 8 + s8] = b[k];
+        });
         __syncthreads();
         // ---- phase 2: interpolation of the nodal fields (lane = (p, field))
-        if (s8 < 7) {
-            double v[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int s = 0; s < 8; ++s) {
-                const double u = sm.sU[s8 * LU + s];
-                for (int k = 0; k < 4; ++k) v[k] += sm.sB[p8 * LB + k * 8 + s] * u;
-            }
-            double *I = sm.sI + p8 * 21;
-            if (s8 < 4) {
-                for (int k = 0; k < 4; ++k) I[4 * s8 + k] = v[k];
-            } else {
-                I[12 + s8] = v[0];
-            }
-        }
+        if (s8 < 7)
+            eights([&](int p) {
+                double v[4] = {0.0, 0.0, 0.0, 0.0};
+                for (int s = 0; s < 8; ++s) {
+                    const double u = sm.sU[s8 * LU + s];
+                    for (int k = 0; k < 4; ++k) v[k] += sm.sB[p * LB + k * 8 + s] * u;
+                }
+                double *I = sm.sI + p * 19;
+                if (s8 < 4) {
+                    for (int k = 0; k < 4; ++k) I[4 * s8 + k] = v[k];
+                } else {
+                    I[12 + s8] = v[0];
+                }
+            });
         __syncthreads();
         // ---- phase 3: the point's table. Lanes r < 3 of point p take row / component
         // r of it; with every component index rotated by r their own row is index
         // 0, so that no register array is indexed by the lane. Lane r = 3 writes
         // the scalars and the continuity row.
-        if (s8 < 4) {
-            const double *I = sm.sI + p8 * 21;
-            const int o[3] = {s8 < 3 ? s8 : 0, s8 < 3 ? (s8 + 1 < 3 ? s8 + 1 : 0) : 1,
-                              s8 < 3 ? (s8 + 2 < 3 ? s8 + 2 : s8 - 1) : 2};
+        const int p3 = NP == 16 ? lane >> 2 : p8, r3 = NP == 16 ? lane & 3 : s8;
+        if constexpr (NP == 16) w = sm.sX[(base & 63) + p3][3];
+        if (r3 < 4) {
+            const double *I = sm.sI + p3 * 19;
+            const int o[3] = {r3 < 3 ? r3 : 0, r3 < 3 ? (r3 + 1 < 3 ? r3 + 1 : 0) : 1,
+                              r3 < 3 ? (r3 + 2 < 3 ? r3 + 2 : r3 - 1) : 2};
             double ut[3], gu[3][3], up[3], acl[3];
             for (int c = 0; c < 3; ++c) {
                 ut[c] = I[4 * o[c]];
@@ -334,9 +358,9 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
             const double pp = -rho * tauC * div;
             const double upg = gG * (up[0] * up[0] + up[1] * up[1] + up[2] * up[2]);
             const double tb = upg > 0.0 ? rsq<double>(upg) : 0.0;
-            double *q = sm.sQ + p8 * PQ_N;
-            if (s8 < 3) {
-                const int c = s8;
+            double *q = sm.sQ + p3 * PQ_N;
+            if (r3 < 3) {
+                const int c = r3;
                 const double sv = up[0] * gu[0][0] + up[1] * gu[0][1] + up[2] * gu[0][2];
                 const double Wt = w * tauM, tbr = tb * rho;
                 q[PQ_T12 + 2 * (c + 1)] = Wt * (rho * ut[0] + up[0]);
@@ -1008,7 +1032,7 @@ __device__ __forceinline__ void asm_item32(const AsmArgs &a, const int64_t item,
 // and fields load while the first is assembled
 template <typename T, int MODE, bool SUB>
 __global__ VMS_ASM_BOUNDS(MODE, SUB) void k_asm2(AsmArgs a) {
-    __shared__ std::conditional_t<MODE == 0, std::conditional_t<SUB, Smem64Sub, Smem64>,
+    __shared__ std::conditional_t<MODE == 0, std::conditional_t<SUB, Smem64Sub<16>, Smem64>,
                                   std::conditional_t<SUB, SmemFSub, SmemF>> sm;
     auto item = [&](int64_t i, const ItemPre *pre) {
         if constexpr (MODE == 0) asm_item64<SUB>(a, i, sm, pre);
@@ -1034,7 +1058,7 @@ template <int MODE, int WPS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void k_asm_batch(
     const AsmArgs *std_args, const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
     unsigned long long *counter) {
-    __shared__ std::conditional_t<MODE == 0, Smem64Sub, SmemFSub> sm;
+    __shared__ std::conditional_t<MODE == 0, Smem64Sub<8>, SmemFSub> sm;
     __shared__ int64_t su;
     __shared__ AsmArgs sa;  // the unit's tree, read from LDS where used
     for (;;) {
