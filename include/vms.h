@@ -401,7 +401,9 @@ void vms_mesh_destroy(vms_mesh *h);
  * vms_assemble (vms_set_overlap) ms[0] and ms[3] are measured on the second
  * stream and ran beside ms[4], which spans from the end of the OUT elements to
  * the end of the call: the device time of the call is ms[1] + ms[2] + ms[4]
- * there, the sum of all five otherwise. */
+ * there, the sum of all five otherwise. So that the stages can be told apart,
+ * an overlapped call with timing on starts its second stream after the OUT
+ * elements. */
 int vms_set_timing(vms_ctx *ctx, int on);
 int vms_last_timing(vms_ctx *ctx, float *ms);
 
@@ -411,11 +413,12 @@ int vms_last_timing(vms_ctx *ctx, float *ms);
  * overlap on, a call that assembles the matrix and has INTERCEPTED items (or
  * weak boundary terms) runs the relabel, the INTERCEPTED items and the surface
  * terms on a second stream that the context owns (created on first use, on the
- * current device, default priority), started by an event after the OUT
- * kernel, while the context stream sums the blocks without late records; the
- * context stream then waits for the second stream and sums the late blocks.
- * When the relabel and the INTERCEPTED items are estimated to take well under
- * the gather, fewer of their workgroups share a CU (extra LDS requested at
+ * current device, default priority), started by an event at the begin of the
+ * call, while the context stream assembles the OUT elements and sums the blocks
+ * without late records; the context stream then waits for the second stream and
+ * sums the late blocks.
+ * Where the call is estimated to end sooner so, fewer workgroups of the
+ * INTERCEPTED items and of the relabel share a CU (extra LDS requested at
  * their launch), which leaves the HBM-bound gather more waves; the estimate
  * uses the numbers of labels and sub-cell points and the gather's bytes at
  * rates measured on MI355X.

@@ -1393,9 +1393,9 @@ static int ensure_side(vms_ctx *c) {
 // One assembly. In order on the context stream: relabel (if asked), OUT
 // elements, INTERCEPTED items, surface terms, CSR blocks, residual. With the
 // matrix and any late work, the overlapped schedule instead forks the relabel,
-// the INTERCEPTED items and the surface terms onto the second stream once the
-// OUT elements are done, sums the blocks without late records meanwhile, joins,
-// and sums the late blocks; every block is summed by the same code in the same
+// the INTERCEPTED items and the surface terms onto the second stream, sums the
+// blocks without late records after the OUT elements meanwhile, joins, and sums
+// the late blocks; every block is summed by the same code in the same
 // order either way, so the outputs are identical.
 // Workgroups per CU of the second stream's kernels (exact relabel, sub-cell
 // items) while they run beside the CSR gather in the overlapped schedule; 0 = no
@@ -1476,6 +1476,25 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         a.el_kk = c->d_el_kk;
     }
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[2], ms));
+    // The second stream's work needs nothing of the OUT elements and starts at once:
+    // the relabel's long chains fill the gaps of their kernel, and more of the items
+    // is left to run beside it than after it. Started after the OUT elements: sphere
+    // FP64 2.64 against 2.42 ms, FP16x2 1.98 / 1.90 ms, 0.2 M octants around two boxes
+    // 1.95 / 1.78 ms, 1.35 M octants 10.0 ms either way. With timing on it does start
+    // after them, so that the stages can be told apart.
+    int late_rc = VMS_OK;
+    auto fork_late = [&]() -> int {
+        HIPCHK(c, hipEventRecord(c->fork, ms));
+        HIPCHK(c, hipStreamWaitEvent(ls, c->fork, 0));
+        if (c->timing) HIPCHK(c, hipEventRecord(c->ev[6], ls));
+        if (relabel) {
+            const int rc = run_subquad(c, false, ls, relabel_cap);
+            if (rc) return rc;
+        }
+        if (c->timing) HIPCHK(c, hipEventRecord(c->ev[7], ls));
+        return VMS_OK;
+    };
+    if (split && !c->timing) late_rc = fork_late();
     // OUT elements: 2x2x2 Gauss points
     a.n_items = c->n_std;
     a.items = c->d_std;
@@ -1484,14 +1503,7 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[3], ms));
-    int late_rc = VMS_OK;
-    if (split) {
-        HIPCHK(c, hipEventRecord(c->fork, ms));
-        HIPCHK(c, hipStreamWaitEvent(ls, c->fork, 0));
-        if (c->timing) HIPCHK(c, hipEventRecord(c->ev[6], ls));
-        if (relabel) late_rc = run_subquad(c, false, ls, relabel_cap);
-        if (c->timing) HIPCHK(c, hipEventRecord(c->ev[7], ls));
-    }
+    if (split && c->timing) late_rc = fork_late();
     // INTERCEPTED elements: kept sub-cell points
     if (late_rc == VMS_OK && c->n_sub_items) {
         a.n_items = c->n_sub_items;
