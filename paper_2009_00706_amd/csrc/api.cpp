@@ -1404,9 +1404,9 @@ static int ensure_side(vms_ctx *c) {
 // items take 1.45 (FP64) or 1.25 times (mixed) as long and the gather runs at its
 // full rate; a relabel at a third of its waves takes 2.7 times as long. So
 // the items are limited where that ends sooner, and the relabel too where all of it
-// still fits beside the gather. Measured, no limit / items / both: two boxes of 1.35
-// M octants FP64 10.9 / 9.9 / 11.5 ms, BF16x3 8.0 / 7.2 / 8.7 ms; of 4.7 M octants 33.2
-// / 30.6 / 35.9 and 24.8 / 21.9 / 26.6 ms; of 12 M octants 71.3 / 68.9 / 67.4 and
+// still fits beside the gather. Measured, no limit / items / both: two boxes in 1.64
+// M octants FP64 10.9 / 9.9 / 11.5 ms, BF16x3 8.0 / 7.2 / 8.7 ms; in 6.0 M octants 33.2
+// / 30.6 / 35.9 and 24.8 / 21.9 / 26.6 ms; in 13 M octants 71.3 / 68.9 / 67.4 and
 // 51.7 / 47.6 / 46.0 ms; sphere (mostly sub-cell points) FP64 2.77 / 3.65 / 4.24 ms.
 // Estimates from rates measured on this GPU: 0.44 ns per sub-cell point over the
 // whole GPU in FP64, 0.31 ns in the mixed forms, 2.0e10 exact labels per second in
@@ -1479,8 +1479,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     // The second stream's work needs nothing of the OUT elements and starts at once:
     // the relabel's long chains fill the gaps of their kernel, and more of the items
     // is left to run beside it than after it. Started after the OUT elements: sphere
-    // FP64 2.64 against 2.42 ms, FP16x2 1.98 / 1.90 ms, 0.2 M octants around two boxes
-    // 1.95 / 1.78 ms, 1.35 M octants 10.0 ms either way. With timing on it does start
+    // FP64 2.64 against 2.42 ms, FP16x2 1.98 / 1.90 ms, 0.27 M octants around two boxes
+    // 1.95 / 1.78 ms, 1.64 M octants 10.0 ms either way. With timing on it does start
     // after them, so that the stages can be told apart.
     int late_rc = VMS_OK;
     auto fork_late = [&]() -> int {

@@ -1181,14 +1181,14 @@ __device__ inline bool res_part(const ResSum &r, unsigned nr) {
 }
 static unsigned res_groups(const ResSum &r) { return r.out ? (unsigned)((r.n_nodes + 255) / 256) : 0u; }
 
-// Bound by HBM (15.6 GB in 3.6 ms for the two-box case of 1.35 M octants in FP64:
+// Bound by HBM (15.6 GB in 3.6 ms for two boxes in 1.64 M octants in FP64:
 // 4.3 TB/s, the rate of a large copy). Workgroups go round the 8 XCDs in turn; the
 // FP64 gather gives each XCD one contiguous range of blocks instead (its grid is a
 // multiple of 8), so that workgroups which share lines of the block headers and
 // of the CSR rows share an L2, and its records, read once, pass the caches by:
 // 16^3 triquadratic elements 482 -> 456 us, the two-box step 11.22 -> 11.07 ms. FP32
 // records are more often still in the caches, where going round finds them
-// sooner (29k hanging-node octants: 686 us so, 706 us by ranges).
+// sooner (166k hanging-node octants: 686 us so, 706 us by ranges).
 template <typename T, int V, bool SKIP_LATE>
 __global__ void k_gather(const T *em, const int64_t *cb_off, const int32_t *contrib,
                          const int64_t *vbase, const int32_t *vstride, int64_t nb, T *vals, ResSum r, unsigned nr) {
