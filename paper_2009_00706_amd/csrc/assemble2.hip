@@ -29,7 +29,7 @@
 // before the contraction run in FP32 on the VALU and the result is written
 // as FP32 (asm_item32).
 //
-// One 64-lane workgroup per element, points in chunks of 8.
+// One 64-lane workgroup per element, points in chunks of 8 (FP64 sub-cell items: 16).
 #include "item_dev.h"
 #include "vms_point.h"
 

@@ -1,6 +1,6 @@
 // Per-point factors and D blocks of the VMS integrand (internal header of
-// libvms, gfx950), shared by the trilinear and the triquadratic element
-// kernels. At a quadrature point of weight W the element matrix gains
+// libvms, gfx950), as the triquadratic element kernel takes them; the trilinear
+// kernels write the same blocks out per entry. At a quadrature point of weight W the element matrix gains
 //   K[(a,i),(b,j)] += sum_{k,l} B[k][a] (W D^{ij}[k][l]) B[l][b],
 // B = [N; dN/dx; dN/dy; dN/dz], and the residual gains
 //   R[(a,i)] += sum_k B[k][a] r^i[k];
