@@ -84,8 +84,11 @@ __device__ inline void triple(double a, double b, double c, double out[4]) {
 }
 
 // Exact sign of det[a-d; b-d; c-d] (rare path: only when the filter fails).
-__device__ __noinline__ int orient3d_exact(const double *a, const double *b, const double *c,
-                                          const double *d) {
+// Coordinates by value, here and below: an array whose address goes to a call is
+// kept in scratch memory by the caller, which then writes it for every test.
+__device__ __noinline__ int orient3d_exact(double a0, double a1, double a2, double b0, double b1, double b2,
+                                          double c0, double c1, double c2, double d0, double d1, double d2) {
+    const double a[3] = {a0, a1, a2}, b[3] = {b0, b1, b2}, c[3] = {c0, c1, c2}, d[3] = {d0, d1, d2};
     double ad[3][2], bd[3][2], cd[3][2];  // [axis][hi, lo]
     for (int k = 0; k < 3; ++k) {
         tsum(a[k], -d[k], ad[k][0], ad[k][1]);
@@ -128,7 +131,7 @@ __device__ inline int orient3d(const double *a, const double *b, const double *c
     const double bound = __dmul_rn((7.0 + 56.0 * 0x1p-53) * 0x1p-53, perm);
     if (det > bound) return 1;
     if (-det > bound) return -1;
-    return orient3d_exact(a, b, c, d);
+    return orient3d_exact(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], d[0], d[1], d[2]);
 }
 
 // exact sign of det[a-c; b-c] in coordinates (i, j)
@@ -167,8 +170,9 @@ __device__ inline int orient2d(const double *a, const double *b, const double *c
 }
 
 // P in the closed triangle abc, P known to lie in its plane
-__device__ __noinline__ bool coplanar_in_triangle(const double *P, const double *a, const double *b,
-                                                 const double *c) {
+__device__ __noinline__ bool coplanar_in_triangle(double P0, double P1, double P2, double a0, double a1, double a2,
+                                                 double b0, double b1, double b2, double c0, double c1, double c2) {
+    const double P[3] = {P0, P1, P2}, a[3] = {a0, a1, a2}, b[3] = {b0, b1, b2}, c[3] = {c0, c1, c2};
     const int pi[3] = {0, 1, 0}, pj[3] = {1, 2, 2};
     for (int k = 0; k < 3; ++k) {
         int s = orient2d(a, b, c, pi[k], pj[k]);
@@ -188,7 +192,9 @@ enum { SEG_MISS = 0, SEG_CROSS = 1, SEG_DEGEN = 2, SEG_ON = 3 };
 __device__ inline int segment_triangle(const double *P, const double *Q, const double *a,
                                        const double *b, const double *c, int sq) {
     int sp = orient3d(a, b, c, P);
-    if (sp == 0) return coplanar_in_triangle(P, a, b, c) ? SEG_ON : SEG_MISS;
+    if (sp == 0)
+        return coplanar_in_triangle(P[0], P[1], P[2], a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2]) ? SEG_ON
+                                                                                                        : SEG_MISS;
     if (sq == 0) return SEG_DEGEN;
     if (sp == sq) return SEG_MISS;
     int e1 = orient3d(P, Q, a, b);

@@ -50,7 +50,8 @@ __device__ inline void wave_sync() {
 // gathered in a queue, so that the exact tests run with full waves too. The
 // outcome per point (crossing parity, degenerate, on the surface) does not
 // depend on the order. One lane per point took 1.33 ms for 10^6 points near the
-// two boxes (48,600 triangles), this takes 0.245 ms.
+// two boxes (48,600 triangles), this 0.245 ms, and 0.143 ms since no coordinates
+// are kept in scratch memory for the exact tests.
 __global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, const double *px, const double *py,
                                                       const double *pz, uint8_t *lab, unsigned long long *ndeg) {
     struct Wave {
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, cons
     wave_sync();
     if (i < n) {
         const unsigned r = w.res[lane];
-        lab[i] = (uint8_t)((r & 4u) ? 1 : ((r & 2u) ? ray_label_degenerate(S, P, ndeg) : (int)(r & 1u)));
+        lab[i] = (uint8_t)((r & 4u) ? 1 : ((r & 2u) ? ray_label_degenerate(S, P[0], P[1], P[2], ndeg) : (int)(r & 1u)));
     }
 }
 

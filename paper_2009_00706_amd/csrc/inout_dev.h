@@ -68,7 +68,10 @@ __device__ __noinline__ static int ray_label_dir(const SurfDev &S, const double 
 }
 
 // label of a point whose ray along x met an edge or a vertex
-__device__ __noinline__ static int ray_label_degenerate(const SurfDev &S, const double *P, unsigned long long *ndeg) {
+// (arguments by value: their addresses would keep them in scratch memory in the caller)
+__device__ __noinline__ static int ray_label_degenerate(SurfDev S, double P0, double P1, double P2,
+                                                        unsigned long long *ndeg) {
+    const double P[3] = {P0, P1, P2};
     bool deg = false;
     for (int d = 1; d < 10; ++d) {
         if (ndeg) atomicAdd(ndeg, 1ull);
@@ -103,7 +106,7 @@ __device__ static int ray_label(const SurfDev &S, const double *P, unsigned long
         if (r == SEG_DEGEN) deg = true;
         else cnt ^= r;
     }
-    return deg ? ray_label_degenerate(S, P, ndeg) : cnt;
+    return deg ? ray_label_degenerate(S, P[0], P[1], P[2], ndeg) : cnt;
 }
 
 __device__ static int local_label(const SurfDev &S, const double *P, const double (*V)[3],
