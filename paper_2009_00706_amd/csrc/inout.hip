@@ -82,14 +82,6 @@ __global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, cons
     }
     for (int k = 0; k < 3; ++k) w.P[lane][k] = P[k];
     w.res[lane] = 0u;
-    int incl = cnt;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
-    }
-    w.off[lane + 1] = incl;
-    if (lane == 0) w.off[0] = 0;
-    const int total = __shfl(incl, 63, 64);
     int nq = 0;  // queued pairs (uniform over the wave)
     auto flush = [&](int from, int m) {
         if (lane < m) {
@@ -105,34 +97,47 @@ __global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, cons
             else if (r) atomicXor(&w.res[o], 1u);
         }
     };
-    wave_sync();
-    for (int k0 = 0; k0 < total; k0 += 64) {
-        const int k = k0 + lane;
-        bool hit = false;
-        int o = 0, t = 0;
-        if (k < total) {
-            for (int b = 32; b > 0; b >>= 1)
-                if (w.off[o + b] <= k) o += b;
-            t = S.bin_tri[w.first[o] + (k - w.off[o])];
-            const double *bx = S.tbox + 6 * (int64_t)t;
-            const double R0 = w.P[o][0], R1 = w.P[o][1], R2 = w.P[o][2];
-            // along -x when the surface's box ends nearer on that side: only the
-            // triangles on that side of the point can be crossed
-            const bool neg = __dsub_rn(R0, S.lo[0]) < __dsub_rn(S.hi[0], R0);
-            hit = !((neg ? bx[0] > R0 : bx[3] < R0) || bx[1] > R1 || bx[4] < R1 || bx[2] > R2 || bx[5] < R2);
+    // all points at once, or one after the other where their pairs could pass 2^31
+    const int rounds = __any(cnt >= 1 << 24) ? 64 : 1;
+    for (int rd = 0; rd < rounds; ++rd) {
+        int incl = rounds == 1 || lane == rd ? cnt : 0;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
         }
-        const unsigned long long m = __ballot(hit);
-        if (hit) {
-            const int at = nq + __popcll(m & ((1ull << lane) - 1ull));
-            w.qp[at] = o;
-            w.qt[at] = t;
-        }
-        nq += __popcll(m);
-        if (nq >= 64) {
-            wave_sync();
-            nq -= 64;
-            flush(nq, 64);
-            wave_sync();
+        wave_sync();
+        w.off[lane + 1] = incl;
+        if (lane == 0) w.off[0] = 0;
+        const int total = __shfl(incl, 63, 64);
+        wave_sync();
+        for (unsigned k0 = 0; k0 < (unsigned)total; k0 += 64) {
+            const unsigned k = k0 + lane;
+            bool hit = false;
+            int o = 0, t = 0;
+            if (k < (unsigned)total) {
+                for (int b = 32; b > 0; b >>= 1)
+                    if ((unsigned)w.off[o + b] <= k) o += b;
+                t = S.bin_tri[w.first[o] + (int)(k - (unsigned)w.off[o])];
+                const double *bx = S.tbox + 6 * (int64_t)t;
+                const double R0 = w.P[o][0], R1 = w.P[o][1], R2 = w.P[o][2];
+                // along -x when the surface's box ends nearer on that side: only the
+                // triangles on that side of the point can be crossed
+                const bool neg = __dsub_rn(R0, S.lo[0]) < __dsub_rn(S.hi[0], R0);
+                hit = !((neg ? bx[0] > R0 : bx[3] < R0) || bx[1] > R1 || bx[4] < R1 || bx[2] > R2 || bx[5] < R2);
+            }
+            const unsigned long long m = __ballot(hit);
+            if (hit) {
+                const int at = nq + __popcll(m & ((1ull << lane) - 1ull));
+                w.qp[at] = o;
+                w.qt[at] = t;
+            }
+            nq += __popcll(m);
+            if (nq >= 64) {
+                wave_sync();
+                nq -= 64;
+                flush(nq, 64);
+                wave_sync();
+            }
         }
     }
     wave_sync();
