@@ -1434,6 +1434,24 @@ static void side_caps(vms_ctx *c, bool relabel, int &items_cap, int &relabel_cap
     relabel_cap = relabel && 2.7 * t_rel + t_half < t_gather ? c->rel_cap : 0;
 }
 
+// Orders the context stream after all that the second stream has been given since
+// the fork, also when the call returns early with an error: its kernels read the
+// caller's fields and write the context's records. Where the join's event cannot be
+// recorded or waited for, the host waits for the stream.
+struct SideJoin {
+    vms_ctx *c;
+    bool pending = false;
+    hipError_t join() {
+        if (!pending) return hipSuccess;
+        hipError_t e = hipEventRecord(c->join, c->side);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, c->join, 0);
+        if (e != hipSuccess) (void)hipStreamSynchronize(c->side);
+        pending = false;
+        return e;
+    }
+    ~SideJoin() { (void)join(); }
+};
+
 static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *resid, uint32_t flags,
                          bool mat) {
     if (!c || !f) return fail(c, VMS_EINVAL, "null context or fields");
@@ -1456,8 +1474,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     if (split) side_caps(c, relabel, items_cap, relabel_cap);
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[0], ms));
     if (relabel && !split) {
-        int rc = run_subquad(c, false, ms);
-        if (rc) return rc;
+        const int rl = run_subquad(c, false, ms);
+        if (rl) return rl;
     }
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[1], ms));
     const bool fp64 = c->prm.precision == VMS_FP64;
@@ -1482,10 +1500,11 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     // FP64 2.64 against 2.42 ms, FP16x2 1.98 / 1.90 ms, 0.27 M octants around two boxes
     // 1.95 / 1.78 ms, 1.64 M octants 10.0 ms either way. With timing on it does start
     // after them, so that the stages can be told apart.
-    int late_rc = VMS_OK;
+    SideJoin side{c};
     auto fork_late = [&]() -> int {
         HIPCHK(c, hipEventRecord(c->fork, ms));
         HIPCHK(c, hipStreamWaitEvent(ls, c->fork, 0));
+        side.pending = true;
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[6], ls));
         if (relabel) {
             const int rc = run_subquad(c, false, ls, relabel_cap);
@@ -1494,7 +1513,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[7], ls));
         return VMS_OK;
     };
-    if (split && !c->timing) late_rc = fork_late();
+    int rc = VMS_OK;
+    if (split && !c->timing && (rc = fork_late())) return rc;
     // OUT elements: 2x2x2 Gauss points
     a.n_items = c->n_std;
     a.items = c->d_std;
@@ -1503,9 +1523,9 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[3], ms));
-    if (split && c->timing) late_rc = fork_late();
+    if (split && c->timing && (rc = fork_late())) return rc;
     // INTERCEPTED elements: kept sub-cell points
-    if (late_rc == VMS_OK && c->n_sub_items) {
+    if (c->n_sub_items) {
         a.n_items = c->n_sub_items;
         a.items = c->d_sub_el;
         a.pt_off = c->d_sub_off;
@@ -1517,7 +1537,7 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, items_cap);
         HIPCHK(c, hipGetLastError());
     }
-    if (late_rc == VMS_OK && c->wbc && c->n_surf_items) {
+    if (c->wbc && c->n_surf_items) {
         // weak boundary terms: records after the sub-cell items
         vmsk::launch_surface(ls, surf_args(c, fp, resid), mat ? 0 : 1, fp64, nullptr);
         HIPCHK(c, hipGetLastError());
@@ -1525,17 +1545,14 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     const void *em = c->d_em;
     if (split) {
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], ls));
-        HIPCHK(c, hipEventRecord(c->join, ls));
-        if (late_rc == VMS_OK) {
-            if (fp64)
-                vmsk::launch_gather_f64(ms, (const double *)em, c->d_cb_off, c->d_contrib, c->d_vbase,
-                                        c->d_vstride, c->n_blocks, (double *)vals, true);
-            else
-                vmsk::launch_gather_f32(ms, (const float *)em, c->d_cb_off, c->d_contrib, c->d_vbase,
-                                        c->d_vstride, c->n_blocks, (float *)vals, true);
-        }
-        HIPCHK(c, hipStreamWaitEvent(ms, c->join, 0));
-        if (late_rc) return late_rc;
+        if (fp64)
+            vmsk::launch_gather_f64(ms, (const double *)em, c->d_cb_off, c->d_contrib, c->d_vbase,
+                                    c->d_vstride, c->n_blocks, (double *)vals, true);
+        else
+            vmsk::launch_gather_f32(ms, (const float *)em, c->d_cb_off, c->d_contrib, c->d_vbase,
+                                    c->d_vstride, c->n_blocks, (float *)vals, true);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, side.join());
         vmsk::launch_gather_list(ms, fp64, em, c->d_cb_off, c->d_contrib, c->d_vbase, c->d_vstride, c->d_late,
                                  c->n_late, vals, res_sum(c, resid));
     } else {
