@@ -126,8 +126,9 @@ def node_xyz(vms, ctx, tree):
         float(1 << tree.max_level) * tree.root_len + np.asarray(tree.origin)
 
 
-# the sources of the element kernel: the recorded traffic holds for this text only
-KERNEL_SOURCES = ("assemble2.hip", "kernels.h", "geom.h", "vms_point.h")
+# the sources of the element kernel (assemble2.hip and the headers it includes): the
+# recorded traffic holds for this text only
+KERNEL_SOURCES = ("assemble2.hip", "item_dev.h", "kernels.h", "geom.h", "vms_point.h")
 
 
 def traffic_for(path, workload, precision):
