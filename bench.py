@@ -532,6 +532,13 @@ def form_errors(torch, m, r):
             "rel_err_jacobian_all_entries": (diff_all / ref_all) ** 0.5, "rel_err_residual": er}
 
 
+def products_before_assembly_pays(t_asm, t_mf, t_sp):
+    """Number of products after which assembling once and multiplying with the
+    matrix is cheaper than the matrix-free action; None where it never is (the
+    product with the matrix is not the faster one)."""
+    return t_asm / (t_mf - t_sp) if t_mf > t_sp else None
+
+
 def jacobian_products(torch, vms, tree, surf, f, prec, reps=20):
     """The two ways to apply the Jacobian inside a Krylov solver: the
     matrix-free action (no matrix) and the CSR product with the assembled
@@ -567,7 +574,7 @@ def jacobian_products(torch, vms, tree, surf, f, prec, reps=20):
     asm.close()
     return {"matrix_free_ms": t_mf, "spmv_ms": t_sp, "assembly_ms": t_asm,
             "rel_diff_matrix_free_vs_spmv": diff,  # over the rows of active nodes
-            "products_before_assembly_pays": t_asm / max(t_mf - t_sp, 1e-9),
+            "products_before_assembly_pays": products_before_assembly_pays(t_asm, t_mf, t_sp),
             "spmv_roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                               "frac": gbs / PEAK_HBM_GBS, "bytes_per_launch": sp_bytes,
                               "kernel": "k_bspmv"},
