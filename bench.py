@@ -259,45 +259,46 @@ def run_single(torch, vms, tree, surf, f, prec, steps, warmup, flags, params=Non
     extra = prepare(asm) if prepare else None
     st = vms.vms_stats(asm.ctx)
     n_active = st["n_out"] + st["n_intercepted"]
-    vms.vms_set_timing(asm.ctx, True)
+    # the timed steps run as a caller's do, with stage timing off (an overlapped call
+    # with it on starts its second stream later); one event per step
+    vms.vms_set_timing(asm.ctx, False)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(steps + 1)]
     for _ in range(warmup):
         asm.assemble(flags=flags)
     torch.cuda.synchronize()
-    stage = np.zeros((steps, 5))
     t0 = time.perf_counter()
     for k in range(steps):
+        ev[k].record(asm.stream)
         asm.assemble(flags=flags)
-        stage[k] = vms.vms_last_timing(asm.ctx)
+    ev[steps].record(asm.stream)
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
-    # the same step in order (every stage alone on the context stream): the
-    # isolated stage times and what the overlapped schedule gains
-    vms.vms_set_overlap(asm.ctx, False)
-    n_io = min(steps, 5)
-    asm.assemble(flags=flags)
-    torch.cuda.synchronize()
-    stage_io = np.zeros((n_io, 5))
-    t2 = time.perf_counter()
-    for k in range(n_io):
-        asm.assemble(flags=flags)
-        stage_io[k] = vms.vms_last_timing(asm.ctx)
-    torch.cuda.synchronize()
-    ms_io = 1e3 * (time.perf_counter() - t2) / n_io
-    vms.vms_set_overlap(asm.ctx, True)
+    dev = np.array([ev[k].elapsed_time(ev[k + 1]) for k in range(steps)])
     # steady state (labels cached), for context
     t1 = time.perf_counter()
     for _ in range(steps):
         asm.assemble(flags=0)
     torch.cuda.synchronize()
     steady = n_active * steps / (time.perf_counter() - t1)
+    n_st = min(steps, 5)
+    stage = staged_steps(torch, vms, asm, flags, n_st)
+    # the same step in order (every stage alone on the context stream): the
+    # isolated stage times and what the overlapped schedule gains
+    vms.vms_set_overlap(asm.ctx, False)
+    asm.assemble(flags=flags)
+    torch.cuda.synchronize()
+    t2 = time.perf_counter()
+    for _ in range(n_st):
+        asm.assemble(flags=flags)
+    torch.cuda.synchronize()
+    ms_io = 1e3 * (time.perf_counter() - t2) / n_st
+    stage_io = staged_steps(torch, vms, asm, flags, n_st)
+    vms.vms_set_overlap(asm.ctx, True)
     asm.assemble(flags=flags)
     torch.cuda.synchronize()
     relabel = vms.vms_relabel_stats(asm.ctx) if surf is not None else None
     vms.vms_sizes(asm.ctx)   # raises if a relabel changed an element's kept-point count
-    # device time of each timed step: the stages on the context stream (the
-    # relabel and INTERCEPTED stages of an overlapped step ran beside the last)
     over = overlapped(st) and not atomic
-    dev = stage[:, 1] + stage[:, 2] + stage[:, 4] if over else stage.sum(1)
     out = {"elapsed": elapsed, "value": n_active * steps / elapsed, "ms_step": 1e3 * elapsed / steps,
            "step_device_ms": {"p10": float(np.percentile(dev, 10)), "p50": float(np.median(dev)),
                               "p90": float(np.percentile(dev, 90))},
@@ -309,6 +310,20 @@ def run_single(torch, vms, tree, surf, f, prec, steps, warmup, flags, params=Non
     return out
 
 
+def staged_steps(torch, vms, asm, flags, n):
+    """Stage times [n][5] of n steps of their own, with stage timing on for them."""
+    vms.vms_set_timing(asm.ctx, True)
+    asm.assemble(flags=flags)
+    torch.cuda.synchronize()
+    stage = np.zeros((n, 5))
+    for k in range(n):
+        asm.assemble(flags=flags)
+        stage[k] = vms.vms_last_timing(asm.ctx)
+    torch.cuda.synchronize()
+    vms.vms_set_timing(asm.ctx, False)
+    return stage
+
+
 def overlapped(st):
     """Whether vms_assemble (matrix, overlap on) takes the overlapped schedule."""
     return st["n_intercepted"] > 0 or st.get("n_surfgp", 0) > 0
@@ -318,9 +333,10 @@ def stage_dict(avg, over=False):
     if over:
         return {"relabel_beside": float(avg[0]), "args": float(avg[1]), "out_elements": float(avg[2]),
                 "intercepted_elements_beside": float(avg[3]), "after_out_elements": float(avg[4]),
-                "note": "overlapped step: relabel and INTERCEPTED items on the second stream, beside "
-                        "the span after the OUT kernel (gather of the other blocks, then the late "
-                        "blocks and the residual); device step = args + OUT + that span"}
+                "note": "overlapped steps of their own, whose second stream (relabel, INTERCEPTED items) "
+                        "starts after the OUT kernel so that the stages can be told apart, beside the "
+                        "gather of the other blocks, then the late blocks and the residual; in the timed "
+                        "steps it starts with the step"}
     return {"relabel": float(avg[0]), "args": float(avg[1]), "out_elements": float(avg[2]),
             "intercepted_elements": float(avg[3]), "csr_gather": float(avg[4])}
 
@@ -693,9 +709,9 @@ def roofline_of(m, prec, vms, traffic):
     isolated time): FP64 against the FP64 peak; the mixed forms against the
     dense BF16/FP16 matrix-core peak of their contraction, with the FP32 vector
     figure beside it (their per-point work and operand splits run on the FP32
-    VALU). The OUT kernel runs alone on the context stream in either schedule:
-    its time is that of the timed steps. The INTERCEPTED kernel of an
-    overlapped step shares the GPU with the gather: its time is that of the
+    VALU). The OUT kernel has the GPU to itself in the staged steps of either
+    schedule: its time is that of the staged steps. The INTERCEPTED kernel of
+    an overlapped step shares the GPU with the gather: its time is that of the
     in-order steps."""
     avg, io, st = m["stage"], m["stage_in_order"], m["stats"]
     if io[3] > io[2]:
@@ -703,7 +719,7 @@ def roofline_of(m, prec, vms, traffic):
         sched = "in-order steps"
     else:
         k_ms, n_pts, kname = avg[2], 8 * st["n_out"], "k_asm2 (OUT elements)"
-        sched = "timed steps"
+        sched = "staged steps"
     if prec == vms.VMS_FP64:
         rf = roofline(k_ms, n_pts, PEAK_FP64_TFLOPS, traffic, kname)
     else:
