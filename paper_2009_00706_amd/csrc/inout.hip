@@ -97,8 +97,10 @@ __global__ __launch_bounds__(256) void k_point_labels(SurfDev S, int64_t n, cons
             else if (r) atomicXor(&w.res[o], 1u);
         }
     };
-    // all points at once, or one after the other where their pairs could pass 2^31
-    const int rounds = __any(cnt >= 1 << 24) ? 64 : 1;
+    // all points at once, or one after the other where their pairs could pass 2^31 (64
+    // bins under 2^16 triangles cannot; above, 64 numberings are little beside the
+    // 1024 and more groups of the one point's pairs)
+    const int rounds = __any(cnt >= 1 << 16) ? 64 : 1;
     for (int rd = 0; rd < rounds; ++rd) {
         int incl = rounds == 1 || lane == rd ? cnt : 0;
         for (int d = 1; d < 64; d <<= 1) {
