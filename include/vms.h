@@ -414,19 +414,25 @@ int vms_last_timing(vms_ctx *ctx, float *ms);
  * weak boundary terms) runs the relabel, the INTERCEPTED items and the surface
  * terms on a second stream that the context owns (created on first use, on the
  * current device, default priority), started by an event at the begin of the
- * call, while the context stream assembles the OUT elements and sums the blocks
- * without late records; the context stream then waits for the second stream and
- * sums the late blocks.
+ * call (after the OUT elements where that is estimated to be better), while the
+ * context stream assembles the OUT elements and sums the blocks without late
+ * records; the context stream then waits for the second stream and sums the
+ * late blocks.
  * Where the call is estimated to end sooner so, fewer workgroups of the
  * INTERCEPTED items and of the relabel share a CU (extra LDS requested at
  * their launch), which leaves the HBM-bound gather more waves; the estimate
- * uses the numbers of labels and sub-cell points and the gather's bytes at
- * rates measured on MI355X.
+ * uses the numbers of OUT elements, labels, background triangles and sub-cell
+ * points and the gather's bytes at rates measured on MI355X.
  * All of the call's work is ordered before later work on the context stream,
  * and the outputs are bit for bit those of the in-order schedule (same
  * records, same per-block summation order). Off: every stage in order on the
- * context stream (isolated stage times). Errors: VMS_EINVAL (null context). */
+ * context stream (isolated stage times). A call that fails waits for the second
+ * stream as one that succeeds does. Errors: VMS_EINVAL (null context). */
 int vms_set_overlap(vms_ctx *ctx, int on);
+/* The limits of the last vms_assemble: workgroups per CU of the INTERCEPTED items
+ * (limits[0]) and of the relabel (limits[1]), 0 where there was none or the call
+ * ran in order. limits: HOST, 2 entries. Errors: VMS_EINVAL (null argument). */
+int vms_overlap_limits(vms_ctx *ctx, int32_t *limits);
 
 /* Scatter of the element matrices in vms_assemble. VMS_SCATTER_RECORDS (the
  * default): every work item writes a 1024-entry record and a gather sums each

@@ -272,6 +272,12 @@ int build_surface(const vms_surface *s, hipStream_t st, SurfaceHost &H, std::str
 
 }  // namespace
 
+// the second stream's share of the GPU in an overlapped call (side_plan)
+struct SidePlan {
+    int items_cap = 0, relabel_cap = 0;
+    bool after_out = false;
+};
+
 struct vms_ctx {
     hipStream_t stream = nullptr;
     std::string err = "no error";
@@ -300,6 +306,9 @@ struct vms_ctx {
     uint8_t *d_sq_level = nullptr, *d_sq_clab = nullptr;
     int64_t *d_bt_off = nullptr;
     std::vector<int32_t> sq_nbt;  // background triangles of each INTERCEPTED element (host)
+    // kept points times background triangles: their sum, and the seconds of the
+    // element with most of them (side_plan)
+    double sq_work = 0, sq_longest = 0;
     // bodies of the surface and their convexity; per background-triangle entry
     // the local index of its body at the element, per element the body mask
     // (0: the normal-based filter is off there)
@@ -310,7 +319,7 @@ struct vms_ctx {
     // learned mode: the INTERCEPTED elements (list positions) at or above the
     // threshold on the background-triangle count, and the others
     int32_t split_bt = -1;
-    int sub_cap = -1, rel_cap = 0;  // workgroups per CU beside the gather (side_caps; -1: not yet set)
+    int sub_cap = -1, rel_cap = 0;  // workgroups per CU beside the gather (side_plan; -1: not yet set)
     int64_t n_sq_net = 0, n_sq_exact = 0;
     int32_t *d_sq_net = nullptr, *d_sq_exact = nullptr;
     int32_t *d_bt_ids = nullptr;
@@ -377,6 +386,7 @@ struct vms_ctx {
     // surface terms beside the summation of the other blocks; fork / join order
     // it after the OUT elements and before the late blocks
     bool overlap = true, last_split = false;
+    SidePlan last_plan;
     // scatter of the element matrices (vms_set_scatter); the atomic mode needs
     // each element's block columns on the device
     uint32_t scatter = VMS_SCATTER_RECORDS;
@@ -1221,6 +1231,11 @@ int vms_create(vms_ctx **out, const vms_octree *tree, const vms_surface *surf,
         rc = run_subquad(c, true, c->stream);
         if (rc) return bail(rc);
         stage("sub-cell quadrature");
+        for (int64_t i = 0; i < c->n_sq; ++i) {
+            const double w = (double)c->sq_nbt[i] * c->sq_cnt[i];
+            c->sq_work += w;
+            c->sq_longest = std::max(c->sq_longest, w * (c->sq_nbt[i] > vmsk::SQ_STAGED ? 30e-9 : 19e-9));
+        }
         // split every element's point list into work items of at most ITEM_PTS
         // points (each item writes its own record; the gathers sum them)
         const int ITEM_PTS = VMS_ITEM_PTS;
@@ -1390,38 +1405,72 @@ static int ensure_side(vms_ctx *c) {
     return VMS_OK;
 }
 
-// One assembly. In order on the context stream: relabel (if asked), OUT
-// elements, INTERCEPTED items, surface terms, CSR blocks, residual. With the
-// matrix and any late work, the overlapped schedule instead forks the relabel,
-// the INTERCEPTED items and the surface terms onto the second stream, sums the
-// blocks without late records after the OUT elements meanwhile, joins, and sums
-// the late blocks; every block is summed by the same code in the same
-// order either way, so the outputs are identical.
-// Workgroups per CU of the second stream's kernels (exact relabel, sub-cell
-// items) while they run beside the CSR gather in the overlapped schedule; 0 = no
-// limit. Without limits they leave few registers to the gather, which gets less
-// than half of its work done beside them; with half of their waves the sub-cell
-// items take 1.45 (FP64) or 1.25 times (mixed) as long and the gather runs at its
-// full rate; a relabel at a third of its waves takes 2.7 times as long. So
-// the items are limited where that ends sooner, and the relabel too where all of it
-// still fits beside the gather. Measured, no limit / items / both: two boxes in 1.64
-// M octants FP64 10.9 / 9.9 / 11.5 ms, BF16x3 8.0 / 7.2 / 8.7 ms; in 6.0 M octants 33.2
-// / 30.6 / 35.9 and 24.8 / 21.9 / 26.6 ms; in 13 M octants 71.3 / 68.9 / 67.4 and
-// 51.7 / 47.6 / 46.0 ms; sphere (mostly sub-cell points) FP64 2.77 / 3.65 / 4.24 ms.
-// Estimates from rates measured on this GPU: 0.44 ns per sub-cell point over the
-// whole GPU in FP64, 0.31 ns in the mixed forms, 2.0e10 exact labels per second in
-// the relabel, the gather's bytes (records read, values written) at 4.3 TB/s
-// (FP64 values) or 3.75 TB/s (FP32).
-static void side_caps(vms_ctx *c, bool relabel, int &items_cap, int &relabel_cap) {
-    items_cap = relabel_cap = 0;
+// How the second stream shares the GPU in the overlapped schedule: workgroups per CU
+// of the sub-cell items and of the exact relabel while they run beside the OUT
+// elements and the CSR gather (0 = no limit), and whether it starts with the call or
+// after the OUT elements.
+//
+// Without limits they leave few registers to the gather, and the call ends about 0.8
+// (FP64) or 0.9 (mixed) of their own time after OUT elements and gather alone would.
+// With half of their waves the items take about one and a half times as long, but
+// the gather runs beside them at its rate, and the call ends at their end or 0.55 of
+// the second stream's own time after OUT elements and gather, whichever is later. So
+// the items are limited where the gather is long enough for them, after what the
+// relabel costs it (FP64: what is left of it when the OUT elements are done; mixed:
+// a third). A relabel with a third of its waves takes its longest element and 1.6
+// times its work, and then that share is 0.42. It finds little room beside the OUT
+// elements: a quarter of its rate in FP64, none in the mixed forms, whose OUT
+// elements fill the LDS. So it is limited too where the items' end stays below the
+// other term even so.
+//
+// The relabel's long chains fill the gaps of the OUT elements' kernel, and the more of
+// the items is done beside it the less is left after it, so the second stream
+// starts with the call: sphere FP64 2.40 against 2.61 ms started after the OUT elements,
+// two boxes in 1.64 M octants 10.0 / 10.9, in 5.96 M 30.6 / 32.8 (but in 0.53 M 3.33 /
+// 3.28, in 10.2 M 54.0 / 53.6). Limited items alone only slow the OUT elements of the
+// mixed forms and start after them, unless they outlast the gather: without
+// relabelling, BF16x3, two boxes in 0.53 M octants 2.29 / 2.23, 1.64 M 6.91 / 6.81, 3.11 M
+// 13.5 / 13.2, 5.96 M 21.1 / 20.6, 10.2 M 38.2 / 37.2 ms; outlasting it, 3.65 M (198,744
+// triangles) 14.4 / 14.7 ms. FP64 is the same either way (9.65 / 9.68, 19.2 / 19.2).
+//
+// Times from rates measured on this GPU: OUT elements 3.6 ns each (FP64); items 0.41
+// (FP64) or 0.30 ns per sub-cell point; the gather's bytes (records read, values
+// written) at 4.35 TB/s (FP64 values) or 3.6 TB/s; the relabel over the whole GPU 6.5 ns
+// per element, 13 ps per candidate point and 8 ps per kept point and background
+// triangle, its longest element 0.15 ms and per kept point and triangle 19 ns, 30
+// where the triangles are not staged in LDS.
+//
+// Measured with relabelling, no limit / items / both, in ms, * the rule's choice:
+//   octants (surface triangles)      FP64                     BF16x3
+//   sphere 0.19 M (5,120)            2.40* / 3.21 / 3.83      1.98* / 2.35 / 2.88
+//   two boxes 0.21 M (6,144)         1.52 / 1.41* / 1.74      1.14* / 1.23 / 1.38
+//   two boxes 0.21 M (198,744)       3.23* / 3.43 / 4.02      2.97* / 3.10 / 3.63
+//   two boxes 0.53 M (21,600)        3.49 / 3.37 / 3.33*      2.41 / 2.32 / 2.30*
+//   two boxes 0.53 M (48,600)        3.53 / 3.42 / 3.35*      2.46 / 2.35* / 2.57
+//   two boxes 0.53 M (198,744)       4.81* / 5.06 / 5.72      4.28* / 4.39 / 4.85
+//   two boxes 0.75 M (48,600)        5.77* / 6.41 / 7.57      4.32* / 4.47 / 5.58
+//   two boxes 1.64 M (48,600)        11.2 / 10.3 / 10.0*      8.24 / 7.45* / 8.02
+//   two boxes 3.11 M (48,600)        20.6 / 19.8 / 19.5*      14.8 / 13.8 / 13.3*
+//   two boxes 3.65 M (21,600)        22.7* / 23.1 / 25.5      17.7 / 17.7* / 19.3
+//   two boxes 3.65 M (198,744)       22.6 / 22.5* / 25.5      17.6 / 17.2* / 19.8
+//   two boxes 5.96 M (48,600)        33.8 / 31.5 / 30.6*      25.3 / 22.6* / 24.7
+//   two boxes 10.19 M (198,744)      56.8 / 54.9 / 54.0*      41.9 / 39.3 / 37.5*
+static SidePlan side_plan(vms_ctx *c, bool relabel) {
+    SidePlan s;
     const bool fp64 = c->prm.precision == VMS_FP64;
     const double vb = fp64 ? 8.0 : 4.0;
-    const double t_items = (double)c->n_subgp * (fp64 ? 0.44e-9 : 0.31e-9);
-    const double t_rel = relabel ? (double)c->n_labelled / 2.0e10 : 0.0;
     const double recs = (double)(c->n_std + c->n_sub_items);
-    const double t_gather = (recs * 1024.0 + (double)c->mesh.nnz) * vb / (fp64 ? 4.3e12 : 3.75e12);
-    const double t_free = t_rel + t_items, t_half = (fp64 ? 1.45 : 1.25) * t_items;
-    if (!(std::max(t_rel + t_half, t_gather) < std::max(t_free, t_gather + 0.55 * t_free))) return;
+    const double t_gather = (recs * 1024.0 + (double)c->mesh.nnz) * vb / (fp64 ? 4.35e12 : 3.6e12);
+    const double t_items = (double)c->n_subgp * (fp64 ? 0.41e-9 : 0.30e-9);
+    const double t_out = 3.6e-9 * (double)c->n_std;
+    double work = 0.0, longest = 0.0;
+    if (relabel) {
+        work = 6.5e-9 * (double)c->n_sq + 13e-12 * (double)c->n_labelled + 8e-12 * c->sq_work;
+        longest = 0.15e-3 + c->sq_longest;
+    }
+    const double t_rel = std::max(work, longest);
+    const double before = fp64 ? 0.8 * t_items + std::max(t_rel - t_out, 0.0) : 0.5 * t_items + 0.35 * t_rel;
+    if (!(before < t_gather)) return s;
     if (c->sub_cap < 0) {
         const int per_cu = vmsk::sub_items_per_cu(fp64 ? 0 : (c->prm.precision == VMS_MIXED_BF16 ? 1 : 2));
         const int w = per_cu / 4;  // waves per SIMD: one-wave workgroups, 4 SIMDs per CU
@@ -1430,8 +1479,11 @@ static void side_caps(vms_ctx *c, bool relabel, int &items_cap, int &relabel_cap
         // caps of 3 or more keep a capped workgroup within 64 KB of LDS
         c->rel_cap = sq >= 9 ? (sq + 2) / 3 : 0;
     }
-    items_cap = c->sub_cap;
-    relabel_cap = relabel && 2.7 * t_rel + t_half < t_gather ? c->rel_cap : 0;
+    s.items_cap = c->sub_cap;
+    s.after_out = !fp64 && !relabel && t_items < t_gather;
+    const double end = longest + 1.6 * work + (fp64 ? 1.55 * t_items - 0.25 * t_out : 1.45 * t_items);
+    if (relabel && end < t_gather + 0.55 * (t_rel + t_items)) s.relabel_cap = c->rel_cap;
+    return s;
 }
 
 // Orders the context stream after all that the second stream has been given since
@@ -1452,6 +1504,13 @@ struct SideJoin {
     ~SideJoin() { (void)join(); }
 };
 
+// One assembly. In order on the context stream: relabel (if asked), OUT
+// elements, INTERCEPTED items, surface terms, CSR blocks, residual. With the
+// matrix and any late work, the overlapped schedule instead forks the relabel,
+// the INTERCEPTED items and the surface terms onto the second stream, sums the
+// blocks without late records after the OUT elements meanwhile, joins, and sums
+// the late blocks; every block is summed by the same code in the same
+// order either way, so the outputs are identical.
 static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *resid, uint32_t flags,
                          bool mat) {
     if (!c || !f) return fail(c, VMS_EINVAL, "null context or fields");
@@ -1470,8 +1529,12 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     }
     hipStream_t ms = c->stream, ls = split ? c->side : c->stream;
     c->last_split = split;
-    int items_cap = 0, relabel_cap = 0;
-    if (split) side_caps(c, relabel, items_cap, relabel_cap);
+    // with timing on the second stream starts after the OUT elements in any case, so
+    // that the stages can be told apart
+    SidePlan plan;
+    if (split) plan = side_plan(c, relabel);
+    const bool late_fork = c->timing || plan.after_out;
+    if (split) c->last_plan = plan;
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[0], ms));
     if (relabel && !split) {
         const int rl = run_subquad(c, false, ms);
@@ -1494,12 +1557,6 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         a.el_kk = c->d_el_kk;
     }
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[2], ms));
-    // The second stream's work needs nothing of the OUT elements and starts at once:
-    // the relabel's long chains fill the gaps of their kernel, and more of the items
-    // is left to run beside it than after it. Started after the OUT elements: sphere
-    // FP64 2.64 against 2.42 ms, FP16x2 1.98 / 1.90 ms, 0.27 M octants around two boxes
-    // 1.95 / 1.78 ms, 1.64 M octants 10.0 ms either way. With timing on it does start
-    // after them, so that the stages can be told apart.
     SideJoin side{c};
     auto fork_late = [&]() -> int {
         HIPCHK(c, hipEventRecord(c->fork, ms));
@@ -1507,14 +1564,14 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         side.pending = true;
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[6], ls));
         if (relabel) {
-            const int rc = run_subquad(c, false, ls, relabel_cap);
+            const int rc = run_subquad(c, false, ls, plan.relabel_cap);
             if (rc) return rc;
         }
         if (c->timing) HIPCHK(c, hipEventRecord(c->ev[7], ls));
         return VMS_OK;
     };
     int rc = VMS_OK;
-    if (split && !c->timing && (rc = fork_late())) return rc;
+    if (split && !late_fork && (rc = fork_late())) return rc;
     // OUT elements: 2x2x2 Gauss points
     a.n_items = c->n_std;
     a.items = c->d_std;
@@ -1523,7 +1580,7 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[3], ms));
-    if (split && c->timing && (rc = fork_late())) return rc;
+    if (split && late_fork && (rc = fork_late())) return rc;
     // INTERCEPTED elements: kept sub-cell points
     if (c->n_sub_items) {
         a.n_items = c->n_sub_items;
@@ -1533,8 +1590,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         a.entries = c->d_entries;
         a.slot0 = c->n_std;
         if (!mat) vmsk::launch_residual(ls, a, true, fp64, nullptr);
-        else if (fp64) vmsk::launch_assemble_f64(ls, a, true, items_cap);
-        else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, items_cap);
+        else if (fp64) vmsk::launch_assemble_f64(ls, a, true, plan.items_cap);
+        else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, plan.items_cap);
         HIPCHK(c, hipGetLastError());
     }
     if (c->wbc && c->n_surf_items) {
@@ -1605,6 +1662,13 @@ int vms_last_timing(vms_ctx *c, float *ms) {
 int vms_set_overlap(vms_ctx *c, int on) {
     if (!c) return fail(nullptr, VMS_EINVAL, "null context");
     c->overlap = on != 0;
+    return VMS_OK;
+}
+
+int vms_overlap_limits(vms_ctx *c, int32_t *limits) {
+    if (!c || !limits) return fail(c, VMS_EINVAL, "null argument");
+    limits[0] = c->last_split ? c->last_plan.items_cap : 0;
+    limits[1] = c->last_split ? c->last_plan.relabel_cap : 0;
     return VMS_OK;
 }
 

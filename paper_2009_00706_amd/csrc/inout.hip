@@ -199,7 +199,7 @@ void launch_point_labels_list(hipStream_t s, const SurfDev &S, const int64_t *id
 
 constexpr int SQ_MAXCELL = 512;  // cells of one level at depth <= 3
 constexpr int SQ_KEYS = 4096;    // key space 8^(D+1) at depth 3
-constexpr int SQ_BTMAX = 64;     // background triangles staged in LDS
+constexpr int SQ_BTMAX = SQ_STAGED;  // background triangles staged in LDS
 
 // Exact label of P by local segments to the element corners V, with the
 // element's background triangles read from LDS (tv: 9 doubles, tb: box);

@@ -101,6 +101,7 @@ struct SubqArgs {
 // that many workgroups share a CU
 void launch_subquad(hipStream_t s, const SurfDev &S, const GeoArgs &g, const SubqArgs &a, int pass,
                     int wg_per_cu = 0);
+constexpr int SQ_STAGED = 64;  // background triangles of an element that the relabel stages in LDS
 // resident workgroups per CU of the exact relabel kernel
 int subquad_per_cu();
 // bad[e] = 1 when vertex corner[e] of triangle t2[e] lies strictly outside the

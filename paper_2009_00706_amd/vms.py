@@ -39,7 +39,7 @@ EXPORTED = ["vms_create", "vms_sizes", "vms_export", "vms_assemble", "vms_apply"
             "vms_q2_last_timing",
             "vms_q2_destroy",
             "vms_mesh_create", "vms_mesh_sizes", "vms_mesh_export", "vms_mesh_destroy",
-            "vms_set_timing", "vms_last_timing", "vms_set_overlap", "vms_set_scatter", "vms_components", "vms_surface_components", "vms_mlp_create", "vms_mlp_get_params",
+            "vms_set_timing", "vms_last_timing", "vms_set_overlap", "vms_overlap_limits", "vms_set_scatter", "vms_components", "vms_surface_components", "vms_mlp_create", "vms_mlp_get_params",
             "vms_mlp_set_margin", "vms_mlp_set_margin_grid", "vms_mlp_grad", "vms_mlp_train", "vms_mlp_adam_step",
             "vms_mlp_predict", "vms_mlp_last_error", "vms_mlp_destroy", "vms_sdf_sample",
             "vms_batch_create", "vms_batch_set_config", "vms_batch_get_config",
@@ -125,6 +125,8 @@ def lib():
         L.vms_relabel_stats.restype = C.c_int
         L.vms_set_overlap.argtypes = [p, C.c_int]
         L.vms_set_overlap.restype = C.c_int
+        L.vms_overlap_limits.argtypes = [p, p]
+        L.vms_overlap_limits.restype = C.c_int
         L.vms_set_scatter.argtypes = [p, u32]
         L.vms_set_scatter.restype = C.c_int
         L.vms_components.argtypes = [p, p, p]
@@ -502,6 +504,14 @@ def inout_release(h):
 def vms_set_overlap(ctx, on=True):
     """Overlapped (default) or in-order schedule of the matrix assembly (same outputs)."""
     _check(lib().vms_set_overlap(ctx, 1 if on else 0), ctx)
+
+
+def vms_overlap_limits(ctx):
+    """Workgroups per CU of the INTERCEPTED items and of the relabel in the last
+    overlapped assembly (0: no limit, or in order)."""
+    v = (C.c_int32 * 2)()
+    _check(lib().vms_overlap_limits(ctx, v), ctx)
+    return v[0], v[1]
 
 
 def vms_components(ctx):

@@ -8,6 +8,9 @@
 * Steps of BiCGStab that end early (rh . v = 0, |s| small, t = 0, omega = 0) and
   GMRES on an operator that closes the space at once: systems of two coupled nodes
   with dyadic entries, where every product and quotient is exact.
+* The second stream of the overlapped schedule unlimited, with limited items, with a
+  limited relabel too, and started after the OUT elements: the limits are the ones
+  meant, and the outputs equal those in order bit for bit.
 * Labels of points whose bin holds more triangles than one numbering of a wave's
   pairs takes.
 """
@@ -144,3 +147,40 @@ def test_labels_where_one_bin_holds_very_many_triangles(env):
     vms.inout_classify(surf, px, py, pz, lab)
     torch.cuda.synchronize()
     assert np.array_equal(lab.cpu().numpy()[sure], want[sure])
+
+
+# geometry, precision, relabel, whether (items, relabel) are limited
+PLANS = [("sphere", "VMS_FP64", 1, (False, False)), ("boxes", "VMS_FP64", 1, (True, True)),
+         ("boxes", "VMS_FP64", 0, (True, False)), ("boxes", "VMS_MIXED_BF16", 1, (True, True)),
+         ("boxes", "VMS_MIXED_BF16", 0, (True, False)),  # starts after the OUT elements
+         ("finer boxes", "VMS_MIXED_FP16", 1, (True, False)), ("finest boxes", "VMS_FP64", 1, (False, False))]
+
+
+@pytest.mark.parametrize("geometry,prec,relabel,limited", PLANS)
+def test_plans_of_the_second_stream(env, geometry, prec, relabel, limited):
+    torch, vms = env
+    n_face = {"boxes": 30, "finer boxes": 45, "finest boxes": 91}
+    tree, surf = I.sphere_workload(4, 7, 4.0, 3, 0.15) if geometry == "sphere" else \
+        I.two_box_workload(5, 9, 8.0, n_face[geometry])
+    asm = context(vms, tree, surf, prec)
+    outs = []
+    for overlap in (False, True, True):
+        vms.vms_set_overlap(asm.ctx, overlap)
+        asm.vals.fill_(float("nan"))
+        asm.resid.fill_(float("nan"))
+        asm.assemble(flags=vms.VMS_RELABEL * relabel)
+        torch.cuda.synchronize()
+        outs.append((asm.vals.clone(), asm.resid.clone()))
+        got = vms.vms_overlap_limits(asm.ctx)
+        print(f"[plans] {geometry} {prec} relabel {relabel} overlap {overlap}: limits {got}", flush=True)
+        assert (got[0] > 0, got[1] > 0) == (limited if overlap else (False, False))
+    for v, r in outs[1:]:
+        assert torch.equal(v, outs[0][0]) and torch.equal(r, outs[0][1])
+    assert torch.isfinite(outs[0][0]).all()
+    vms.vms_sizes(asm.ctx)
+    asm.close()
+
+
+def test_overlap_limits_reject_null():
+    from paper_2009_00706_amd import vms
+    assert vms.lib().vms_overlap_limits(None, None) == vms.VMS_EINVAL

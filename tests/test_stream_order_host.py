@@ -21,6 +21,7 @@ S = C.CDLL(sys.argv[2], C.RTLD_GLOBAL)   # before libvms: its HIP calls bind her
 S.stand_in_log.restype = C.c_char_p
 from paper_2009_00706_amd import inputs as I, vms
 kernel, call, nth, timing, prec = sys.argv[3].encode(), sys.argv[4].encode(), int(sys.argv[5]), int(sys.argv[6]), int(sys.argv[7])
+flags = int(sys.argv[8])
 CTX = 0x10
 S.stand_in_config(5, 9)
 t = I.uniform_octree(3)
@@ -35,11 +36,11 @@ vals, res = np.zeros(sz["nnz"]), np.zeros(sz["n_rows"])
 vms.vms_set_timing(ctx, timing)
 L = vms.lib()
 S.stand_in_reset(b"", b"", 0)
-assert L.vms_assemble(ctx, C.byref(F), vals.ctypes.data, res.ctypes.data, vms.VMS_RELABEL) == 0
+assert L.vms_assemble(ctx, C.byref(F), vals.ctypes.data, res.ctypes.data, flags) == 0
 print("clean")
 print(S.stand_in_log().decode(), end="")
 S.stand_in_reset(kernel, call, nth)
-rc = L.vms_assemble(ctx, C.byref(F), vals.ctypes.data, res.ctypes.data, vms.VMS_RELABEL)
+rc = L.vms_assemble(ctx, C.byref(F), vals.ctypes.data, res.ctypes.data, flags)
 print("failed", rc)
 print(S.stand_in_log().decode(), end="")
 """
@@ -55,8 +56,9 @@ def stand_in(tmp_path_factory):
     return so
 
 
-def run(stand_in, kernel, call, nth, timing, prec):
-    r = subprocess.run([sys.executable, "-c", _PROBE, ROOT, stand_in, kernel, call, str(nth), str(int(timing)), str(prec)],
+def run(stand_in, kernel, call, nth, timing, prec, flags=1):
+    r = subprocess.run([sys.executable, "-c", _PROBE, ROOT, stand_in, kernel, call, str(nth), str(int(timing)), str(prec),
+                        str(flags)],
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     lines = r.stdout.splitlines()
@@ -99,3 +101,19 @@ def test_second_stream_is_joined_on_errors(stand_in, timing, kernel, call, nth, 
     assert unjoined(clean) == []
     assert rc == -3                     # VMS_EHIP
     assert unjoined(log) == [], log
+
+
+@pytest.mark.parametrize("prec,relabel,timing,after_out", [
+    (0, 1, False, False), (0, 0, False, False), (1, 1, False, False), (1, 0, False, True),
+    (0, 1, True, True), (1, 0, True, True)])
+def test_where_the_second_stream_starts(stand_in, prec, relabel, timing, after_out):
+    """With the call; after the OUT elements with timing on, and for limited items
+    alone in the mixed forms (few sub-cell points here: the gather outlasts them)."""
+    clean, _, _ = run(stand_in, "", "", 0, timing, prec, relabel)
+    side = next(op[1] for op in clean if op[0] == "launch" and op[1] != "10")
+    forked = next(i for i, op in enumerate(clean) if op[0] == "wait" and op[1] == side)
+    event = clean[forked][2]
+    recorded = max(i for i, op in enumerate(clean[:forked]) if op[:2] == ["record", event])
+    out = next(i for i, op in enumerate(clean) if op[0] == "launch" and op[1] == "10" and "k_asm2" in op[2])
+    assert (recorded > out) == after_out
+    assert unjoined(clean) == []
