@@ -334,6 +334,7 @@ struct vms_ctx {
     int32_t *d_sub_el = nullptr, *d_sub_cnt = nullptr;
     int64_t *d_sub_off = nullptr;
     std::vector<int32_t> std_el;  // host copy of the OUT-element list
+    int64_t out_resident = 0;     // workgroups of OUT elements that the GPU holds at once
     // weak boundary terms (eq. weakbc): surface Gauss points, one item per
     // element holding points (records after the sub-cell items)
     bool wbc = false;
@@ -1267,6 +1268,7 @@ int vms_create(vms_ctx **out, const vms_octree *tree, const vms_surface *surf,
     for (int64_t e = 0; e < E; ++e)
         if (c->markers[e] == 0) stdl.push_back((int32_t)e);
     c->n_std = (int64_t)stdl.size();
+    c->out_resident = vmsk::out_items_resident((int)prm->precision);
     std::vector<int32_t> inact;
     for (int64_t n = 0; n < m.n_nodes; ++n)
         if (!m.node_active[n]) inact.push_back((int32_t)n);
@@ -1576,8 +1578,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     a.n_items = c->n_std;
     a.items = c->d_std;
     if (!mat) vmsk::launch_residual(ms, a, false, fp64, nullptr);
-    else if (fp64) vmsk::launch_assemble_f64(ms, a, false);
-    else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16);
+    else if (fp64) vmsk::launch_assemble_f64(ms, a, false, 0, c->out_resident);
+    else vmsk::launch_assemble_mixed(ms, a, false, c->prm.precision == VMS_MIXED_FP16, 0, c->out_resident);
     HIPCHK(c, hipGetLastError());
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[3], ms));
     if (split && late_fork && (rc = fork_late())) return rc;
@@ -1590,8 +1592,8 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
         a.entries = c->d_entries;
         a.slot0 = c->n_std;
         if (!mat) vmsk::launch_residual(ls, a, true, fp64, nullptr);
-        else if (fp64) vmsk::launch_assemble_f64(ls, a, true, plan.items_cap);
-        else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, plan.items_cap);
+        else if (fp64) vmsk::launch_assemble_f64(ls, a, true, plan.items_cap, 0);
+        else vmsk::launch_assemble_mixed(ls, a, true, c->prm.precision == VMS_MIXED_FP16, plan.items_cap, 0);
         HIPCHK(c, hipGetLastError());
     }
     if (c->wbc && c->n_surf_items) {

@@ -397,6 +397,8 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
         }
         __syncthreads();
         // ---- phase 4: D entries, stage 1, stage 2
+        // an odd tail runs a point of weight zero (a loop to np: 6.02 -> 6.11 ms for the
+        // sub-cell items of the 721k-octant sphere)
         const int n2 = SUB ? (np + 1) & ~1 : 8;
 #pragma unroll 1
         for (int p = 0; p < n2; ++p) {
@@ -1364,18 +1366,36 @@ int sub_items_per_cu(int precision) {
     return n;
 }
 
-// OUT elements go two per workgroup (the second one's loads in flight while the
-// first is assembled) only where one each would give more workgroups than the
-// GPU holds at once; below that two in a row only lengthen the one round of
-// workgroups
-static dim3 item_grid(AsmArgs &a, bool sub) {
-    a.pair = !sub && a.n_items > 256 * 12;
-    return dim3((unsigned)(a.pair ? (a.n_items + 1) / 2 : a.n_items));
+int64_t out_items_resident(int precision) {
+    const void *k = precision == 0 ? (const void *)&k_asm2<double, 0, false>
+                    : precision == 1 ? (const void *)&k_asm2<float, 1, false>
+                                     : (const void *)&k_asm2<float, 2, false>;
+    int n = 0, dev = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 64, 0) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return (int64_t)n * cus;
 }
 
-void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu) {
+// OUT elements go two per workgroup (the second one's loads in flight while the
+// first is assembled) only where the GPU goes through many rounds of workgroups: over
+// four times the number it holds at once. Below that the workgroups of the next
+// round load while others compute, and two in a row only lengthen the last round. The
+// FP64 form, with its longer elements, also takes two where one each would leave a
+// second round nearly empty. Measured, one / two per workgroup, us:
+//   elements    3072         3584         4096         8000         13,824       32,768       262,144
+//   FP64        26.6 / 26.8  28.6 / 27.0  29.7 / 31.3  37.5 / 37.9  60.5 / 59.3  120 / 117    916 / 872
+//   BF16x3      19.7 / 22.9  22.2 / 24.0  23.5 / 25.2  32.0 / 32.6  47.3 / 48.0  90.1 / 87.9  611 / 594
+//   FP16x2      19.1 / 21.8  21.5 / 23.0  22.5 / 24.4  30.8 / 31.5  44.8 / 45.4  87.1 / 85.2  590 / 562
+static dim3 item_grid(AsmArgs &a, bool sub, bool fp64, int64_t resident) {
+    const int64_t n = a.n_items;
+    a.pair = !sub && (n > 4 * resident || (fp64 && n > resident && n < resident + resident / 5));
+    return dim3((unsigned)(a.pair ? (n + 1) / 2 : n));
+}
+
+void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu, int64_t resident) {
     if (a.n_items <= 0) return;
-    const dim3 grid = item_grid(a, sub), block(64);
+    const dim3 grid = item_grid(a, sub, true, resident), block(64);
     if (sub)
         hipLaunchKernelGGL((k_asm2<double, 0, true>), grid, block,
                            lds_for_cap((const void *)&k_asm2<double, 0, true>, wg_per_cu), s, a);
@@ -1383,9 +1403,9 @@ void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu) {
         hipLaunchKernelGGL((k_asm2<double, 0, false>), grid, block, 0, s, a);
 }
 
-void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu) {
+void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu, int64_t resident) {
     if (a.n_items <= 0) return;
-    const dim3 grid = item_grid(a, sub), block(64);
+    const dim3 grid = item_grid(a, sub, false, resident), block(64);
 #define VMS_L(MODE)                                                                             \
     do {                                                                                        \
         if (sub)                                                                                \

@@ -163,8 +163,8 @@ inline void set_params(AsmArgs &a, double rho, double mu, double dt, double thet
 }
 // wg_per_cu > 0 (sub-cell items only): dynamic LDS so that at most that many
 // workgroups share a CU, leaving the rest of its waves to another stream's
-// kernel
-void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu = 0);
+// kernel; resident (OUT elements only): out_items_resident of the form
+void launch_assemble_f64(hipStream_t s, AsmArgs a, bool sub, int wg_per_cu, int64_t resident);
 
 // one unit of the persistent batched assembly: items [first, first + count) of
 // tree `tree`'s OUT-element list (sub = 0) or sub-cell work-item list (sub = 1)
@@ -180,10 +180,12 @@ struct BatchUnit {
 void launch_assemble_batch(hipStream_t s, int precision, const AsmArgs *std_args,
                            const AsmArgs *sub_args, const BatchUnit *units, int64_t n_units,
                            unsigned long long *counter, int n_groups, int n_cu);
-void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu = 0);
+void launch_assemble_mixed(hipStream_t s, AsmArgs a, bool sub, int fp16, int wg_per_cu, int64_t resident);
 // resident workgroups per CU of the sub-cell item kernel of a precision form
 // (0 FP64, 1 BF16x3, 2 FP16x2; with the matrix), from its registers and LDS
 int sub_items_per_cu(int precision);
+// workgroups of the OUT elements' kernel that the current device holds at once
+int64_t out_items_resident(int precision);
 // dynamic LDS that holds a kernel to at most wg_per_cu resident workgroups per CU
 size_t lds_for_cap(const void *kernel, int wg_per_cu);
 

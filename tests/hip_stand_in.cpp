@@ -5,7 +5,7 @@
 // split_x) and the number of kept points of an INTERCEPTED element. A launch of a
 // chosen kernel, or a chosen call, can be made to fail.
 //
-// Log lines: "launch STREAM KERNEL", "record EVENT STREAM", "wait STREAM EVENT",
+// Log lines: "launch STREAM KERNEL GRID", "record EVENT STREAM", "wait STREAM EVENT",
 // "sync STREAM".
 #include "kernels.h"
 
@@ -74,11 +74,12 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *s, hipStream_t *s
     *g = g_grid; *b = g_block; *s = g_shmem; *st = g_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t st) {
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t st) {
     const std::string &k = g_name[f];
     if (!g_fail_kernel.empty() && k.find(g_fail_kernel) != std::string::npos && g_fail_nth > 0 && --g_fail_nth == 0)
         return g_last = hipErrorLaunchFailure;
-    note("launch %lx %s\n", st, k.c_str());
+    note("launch %lx %s", st, k.c_str());
+    g_log += " " + std::to_string(grid.x) + "\n";
     if (k.find("k_vertex_labels") != std::string::npos) {
         const int64_t n = *(const int64_t *)args[2];
         const int32_t *ix = *(const int32_t *const *)args[3];

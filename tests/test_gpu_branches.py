@@ -11,6 +11,9 @@
 * The second stream of the overlapped schedule unlimited, with limited items, with a
   limited relabel too, and started after the OUT elements: the limits are the ones
   meant, and the outputs equal those in order bit for bit.
+* OUT elements two per workgroup, the last of an odd count alone, in every form: the
+  matrix against the matrix-free action (FP64 1e-12, mixed 1e-5 of the norm: sums of
+  under 10^3 products in FP64, FP32 products of under 10^2 terms).
 * Labels of points whose bin holds more triangles than one numbering of a wave's
   pairs takes.
 """
@@ -184,3 +187,25 @@ def test_plans_of_the_second_stream(env, geometry, prec, relabel, limited):
 def test_overlap_limits_reject_null():
     from paper_2009_00706_amd import vms
     assert vms.lib().vms_overlap_limits(None, None) == vms.VMS_EINVAL
+
+
+@pytest.mark.parametrize("prec,tol", [("VMS_FP64", 1e-12), ("VMS_MIXED_BF16", 1e-5), ("VMS_MIXED_FP16", 1e-5)])
+def test_out_elements_two_per_workgroup(env, prec, tol):
+    torch, vms = env
+    tree = I.refined_octree(5, 5, lambda x, y, z, h, l: np.zeros(x.shape, bool), ext=(27, 27, 25))
+    assert tree.n == 18225  # over four rounds of 16 workgroups on each of 256 CUs
+    asm = context(vms, tree, None, prec)
+    asm.vals.fill_(float("nan"))
+    asm.assemble()
+    beside = asm.resid.clone()
+    asm.apply()
+    x = torch.as_tensor(np.random.default_rng(6).normal(size=asm.sizes["n_rows"]), device="cuda")
+    a, b = asm.spmv(x), asm.jacobian_action(x)
+    torch.cuda.synchronize()
+    err = (torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b)).item()
+    res = (torch.linalg.vector_norm(asm.resid - beside) / torch.linalg.vector_norm(beside)).item()
+    print(f"[two] {prec}: J x {err:.1e}, residual {res:.1e}", flush=True)
+    assert err <= tol and res <= 2e-13
+    if prec != "VMS_FP64":
+        assert torch.equal(asm.resid, beside)
+    asm.close()

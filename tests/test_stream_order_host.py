@@ -1,10 +1,11 @@
-"""CPU test of the overlapped schedule's stream order when something fails.
+"""CPU tests of what vms_assemble launches, and where.
 
-The second stream's kernels read the caller's fields and write the context's
+The overlapped schedule when something fails: the second stream's kernels read the caller's fields and write the context's
 records, so whatever vms_assemble has queued there must be waited for by the
 context stream before it returns, an error included. libvms runs against a host
 stand-in of the HIP runtime that logs the order of the streams and lets one
-launch or call fail; no device is used."""
+launch or call fail; no device is used. (The stand-in holds 12 workgroups of
+every kernel on each of 256 CUs: 3072.)"""
 import os
 import subprocess
 import sys
@@ -117,3 +118,38 @@ def test_where_the_second_stream_starts(stand_in, prec, relabel, timing, after_o
     out = next(i for i, op in enumerate(clean) if op[0] == "launch" and op[1] == "10" and "k_asm2" in op[2])
     assert (recorded > out) == after_out
     assert unjoined(clean) == []
+
+
+_GRID_PROBE = r"""
+import ctypes as C, sys
+import numpy as np
+sys.path.insert(0, sys.argv[1])
+S = C.CDLL(sys.argv[2], C.RTLD_GLOBAL)
+S.stand_in_log.restype = C.c_char_p
+from paper_2009_00706_amd import inputs as I, vms
+for prec in (0, 1, 2):
+    for ext in ((16, 16, 12), (16, 14, 14), (16, 16, 14), (16, 16, 15), (24, 32, 16), (25, 23, 23)):
+        t = I.refined_octree(5, 5, lambda x, y, z, h, l: np.zeros(x.shape, bool), ext=ext)
+        ctx = vms.vms_create(t, None, vms.make_params(precision=prec), stream=0x10)
+        sz = vms.vms_sizes(ctx)
+        f = np.zeros(sz["n_nodes"])
+        F = vms.Fields(*([f.ctypes.data] * 7))
+        vals, res = np.zeros(sz["nnz"]), np.zeros(sz["n_rows"])
+        S.stand_in_reset(b"", b"", 0)
+        assert vms.lib().vms_assemble(ctx, C.byref(F), vals.ctypes.data, res.ctypes.data, 0) == 0
+        print(prec, t.n, next(l.split()[3] for l in S.stand_in_log().decode().splitlines() if "k_asm2" in l))
+        vms.vms_destroy(ctx)
+"""
+
+
+def test_out_elements_per_workgroup(stand_in):
+    """One OUT element per workgroup up to four rounds of workgroups, two above
+    (the last of an odd count alone); FP64 also two where one each would leave a
+    second round nearly empty."""
+    r = subprocess.run([sys.executable, "-c", _GRID_PROBE, ROOT, stand_in], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    got = {tuple(map(int, x.split()[:2])): int(x.split()[2]) for x in r.stdout.splitlines()}
+    one = {3072: 3072, 3136: 3136, 3584: 3584, 3840: 3840, 12288: 12288, 13225: 6613}
+    want = {(p, n): g for p in (0, 1, 2) for n, g in one.items()}
+    want.update({(0, 3136): 1568, (0, 3584): 1792})
+    assert got == want
