@@ -135,10 +135,10 @@ __device__ inline void load_pre2(const AsmArgs &a, int64_t i0, int64_t i1, bool 
 // MFMA, about 30 FP64 operations and 20 LDS reads for the D entries; with the
 // blocks evaluated in two divergent passes, written to LDS (17.2 KB per
 // workgroup, 2.25 waves per SIMD) and read back, the OUT elements of the
-// 194k-octant sphere took 0.625 ms and its sub-cell items 2.19 ms; now 0.504 and
-// 1.65 ms with 9.7 and 20.2 KB. The point tables (a quarter of the sub-cell items'
+// 194k-octant sphere took 0.63 ms and its sub-cell items 2.2 ms; now 0.47 and 1.50 ms
+// with 9.7 and 20.5 KB. The point tables (a quarter of the sub-cell items'
 // VALU work) take four lanes per point: 16 points at a time fill the wave, in what
-// LDS two waves per SIMD leave (8 at a time: 1.72 ms). An OUT element has only 8
+// LDS two waves per SIMD leave (8 at a time: 4% longer). An OUT element has only 8
 // points, and those of two elements at once would cost a wave per SIMD; the batch
 // kernel, which serves both, keeps 8 (8 trees of 30k octants: 3.59 ms, 3.85 at 16).
 #define PQ_T12 0   // (T1, T2)[r], pairs
@@ -502,9 +502,9 @@ __device__ __forceinline__ void asm_item64(const AsmArgs &a, const int64_t item,
 // the D blocks of two test components are there at a time (4.2 KB instead of
 // 8.8), all arrays are in groups of four read and written as 16 bytes, and the
 // record leaves through LDS in whole lines: 8.8 KB and 126 VGPRs, four waves per
-// SIMD (13 KB and three before). Steps: 52k-octant adaptive mesh BF16x3 0.817 ->
-// 0.695 ms, 194k-octant sphere FP16x2 2.47 -> 2.07 ms, 878k-octant sphere BF16x3
-// 9.00 -> 7.84 ms.
+// SIMD (13 KB and three before). Steps, then: adaptive mesh of 165,656 octants BF16x3
+// 0.817 -> 0.695 ms, 194k-octant sphere FP16x2 2.47 -> 2.07 ms, sphere of 721,169
+// octants BF16x3 9.00 -> 7.84 ms.
 #define FQ_UT 0    // u_theta, W
 #define FQ_UP 4    // u', tau_M
 #define FQ_Y 8     // Y, taubar
@@ -1209,8 +1209,10 @@ __device__ inline bool res_part(const ResSum &r, unsigned nr) {
 }
 static unsigned res_groups(const ResSum &r) { return r.out ? (unsigned)((r.n_nodes + 255) / 256) : 0u; }
 
-// Bound by HBM (15.6 GB in 3.6 ms for two boxes in 1.64 M octants in FP64:
-// 4.3 TB/s, the rate of a large copy). Workgroups go round the 8 XCDs in turn; the
+// Bound by HBM: records and values alone are 15.8 GB in 3.6 ms for two boxes in
+// 1.64 M octants in FP64; with lists and lines read again the counters see 5.4 TB/s
+// on 10.2 M octants (a large copy reaches 4.9 TB/s on this GPU, reads alone 6.1).
+// Workgroups go round the 8 XCDs in turn; the
 // FP64 gather gives each XCD one contiguous range of blocks instead (its grid is a
 // multiple of 8), so that workgroups which share lines of the block headers and
 // of the CSR rows share an L2, and its records, read once, pass the caches by:

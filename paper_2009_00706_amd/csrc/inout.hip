@@ -249,7 +249,7 @@ __device__ static int local_label_lds(const SurfDev &S, const double *P, const d
 // triangle planes are tabulated once, and a segment that does not cross costs one
 // test instead of two. Three waves per SIMD: four spill the predicates'
 // registers, two leave the chains' latency open. Relabelling and assembly of the
-// sphere (4 M sub-cell points) took 2.92 ms before, now 2.79 ms; 2.88 ms at two
+// sphere (4 M sub-cell points), then: 2.92 ms before, 2.79 ms so, 2.88 ms at two
 // waves, 3.26 ms at four.
 template <int FILT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8)))

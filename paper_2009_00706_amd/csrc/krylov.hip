@@ -8,7 +8,8 @@
 // preconditioned copy, coefficients that only the device needs stay there, and
 // the host reads one set of sums per step, written into its own memory by the
 // kernel that forms them. Assembly and 30 GMRES steps on 92127 nodes (FP64): 7.57
-// ms with a kernel per operation and a wait per product, 5.15 ms so; per step then
+// ms with a kernel per operation and a wait per product, 5.15 ms so (4.85 ms with the
+// assembly as it is now); per step
 // 52 us for the matrix product (6 TB/s), 35 us for the three sweeps (16 vectors on
 // average, 4.7 TB/s) and 18 us for their sums and the next vector.
 #include "kernels.h"

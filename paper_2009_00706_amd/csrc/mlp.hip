@@ -49,7 +49,7 @@ void Filter::release() {
 // gradient. The partials are summed in a fixed order (the
 // result repeats bit for bit). One workgroup per 32 samples with outer products
 // on the VALU, every silu recomputed for each use and 12,545 atomic additions
-// per workgroup took 2.03 ms on 65,536 samples, this takes 0.068 + 0.020 ms
+// per workgroup took 2.03 ms on 65,536 samples, this takes 0.069 + 0.012 ms
 // (gradient error against 64 bits 6.7e-7 and 2e-7).
 
 constexpr int TS = 64;    // samples per tile
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // grad = sum of the np partial gradients, losses likewise (the last block), in a
 // fixed order. 64 parameters per block, a wave over every 16th partial, then the
-// 16 waves in order. 512 partials of 35 KB: 11.8 us; 32 parameters and 8 threads
+// 16 waves in order. 512 partials of 50 KB: 11.8 us; 32 parameters and 8 threads
 // each, with the losses added by one thread, 20.4 us.
 constexpr int GS_W = 16;
 __global__ __launch_bounds__(64 * GS_W) void k_grad_sum(const float *part, const double *loss_part, int np, float *grad,
