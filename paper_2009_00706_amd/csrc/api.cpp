@@ -1536,7 +1536,7 @@ static int assemble_impl(vms_ctx *c, const vms_fields *f, void *vals, double *re
     SidePlan plan;
     if (split) plan = side_plan(c, relabel);
     const bool late_fork = c->timing || plan.after_out;
-    if (split) c->last_plan = plan;
+    if (mat) c->last_plan = plan;
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[0], ms));
     if (relabel && !split) {
         const int rl = run_subquad(c, false, ms);
@@ -1669,8 +1669,8 @@ int vms_set_overlap(vms_ctx *c, int on) {
 
 int vms_overlap_limits(vms_ctx *c, int32_t *limits) {
     if (!c || !limits) return fail(c, VMS_EINVAL, "null argument");
-    limits[0] = c->last_split ? c->last_plan.items_cap : 0;
-    limits[1] = c->last_split ? c->last_plan.relabel_cap : 0;
+    limits[0] = c->last_plan.items_cap;
+    limits[1] = c->last_plan.relabel_cap;
     return VMS_OK;
 }
 

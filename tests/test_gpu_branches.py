@@ -177,6 +177,8 @@ def test_plans_of_the_second_stream(env, geometry, prec, relabel, limited):
         got = vms.vms_overlap_limits(asm.ctx)
         print(f"[plans] {geometry} {prec} relabel {relabel} overlap {overlap}: limits {got}", flush=True)
         assert (got[0] > 0, got[1] > 0) == (limited if overlap else (False, False))
+    asm.apply()   # has no second stream: the limits stay those of the assembly
+    assert vms.vms_overlap_limits(asm.ctx) == got
     for v, r in outs[1:]:
         assert torch.equal(v, outs[0][0]) and torch.equal(r, outs[0][1])
     assert torch.isfinite(outs[0][0]).all()
