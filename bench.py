@@ -336,7 +336,7 @@ def stage_dict(avg, over=False):
                 "note": "overlapped steps of their own, whose second stream (relabel, INTERCEPTED items) "
                         "starts after the OUT kernel so that the stages can be told apart, beside the "
                         "gather of the other blocks, then the late blocks and the residual; in the timed "
-                        "steps it starts with the step"}
+                        "steps it starts with the step unless it then gains nothing"}
     return {"relabel": float(avg[0]), "args": float(avg[1]), "out_elements": float(avg[2]),
             "intercepted_elements": float(avg[3]), "csr_gather": float(avg[4])}
 

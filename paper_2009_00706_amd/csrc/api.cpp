@@ -1426,14 +1426,15 @@ static int ensure_side(vms_ctx *c) {
 // other term even so.
 //
 // The relabel's long chains fill the gaps of the OUT elements' kernel, and the more of
-// the items is done beside it the less is left after it, so the second stream
+// the items is done beside it the less is left after the gather, so the second stream
 // starts with the call: sphere FP64 2.40 against 2.61 ms started after the OUT elements,
-// two boxes in 1.64 M octants 10.0 / 10.9, in 5.96 M 30.6 / 32.8 (but in 0.53 M 3.33 /
-// 3.28, in 10.2 M 54.0 / 53.6). Limited items alone only slow the OUT elements of the
-// mixed forms and start after them, unless they outlast the gather: without
-// relabelling, BF16x3, two boxes in 0.53 M octants 2.29 / 2.23, 1.64 M 6.91 / 6.81, 3.11 M
-// 13.5 / 13.2, 5.96 M 21.1 / 20.6, 10.2 M 38.2 / 37.2 ms; outlasting it, 3.65 M (198,744
-// triangles) 14.4 / 14.7 ms. FP64 is the same either way (9.65 / 9.68, 19.2 / 19.2).
+// two boxes in 1.64 M octants 10.0 / 10.9, in 5.96 M 30.6 / 32.8. Where all of it, limited,
+// ends before the gather in either case, it would only slow the OUT elements, and
+// starts after them: 0.53 M 3.33 / 3.28, 3.11 M 19.5 / 19.3, 10.2 M 54.0 / 53.6 ms. In the
+// mixed forms that holds for limited items alone unless their unlimited time
+// outlasts the gather: without relabelling, BF16x3, 0.53 M 2.29 / 2.23, 1.64 M 6.91 /
+// 6.81, 3.11 M 13.5 / 13.2, 5.96 M 21.1 / 20.6, 10.2 M 38.2 / 37.2 ms; outlasting it, 3.65 M
+// (198,744 triangles) 14.4 / 14.7 ms.
 //
 // Times from rates measured on this GPU: OUT elements 3.6 ns each (FP64); items 0.41
 // (FP64) or 0.30 ns per sub-cell point; the gather's bytes (records read, values
@@ -1482,9 +1483,11 @@ static SidePlan side_plan(vms_ctx *c, bool relabel) {
         c->rel_cap = sq >= 9 ? (sq + 2) / 3 : 0;
     }
     s.items_cap = c->sub_cap;
-    s.after_out = !fp64 && !relabel && t_items < t_gather;
-    const double end = longest + 1.6 * work + (fp64 ? 1.55 * t_items - 0.25 * t_out : 1.45 * t_items);
-    if (relabel && end < t_gather + 0.55 * (t_rel + t_items)) s.relabel_cap = c->rel_cap;
+    // the second stream's end after the OUT elements', both limited
+    const double end = (relabel ? longest + 1.6 * work : 0.0) + (fp64 ? 1.55 : 1.45) * t_items;
+    const double beside_out = fp64 ? 0.25 * t_out : 0.0;
+    if (relabel && end - beside_out < t_gather + 0.55 * (t_rel + t_items)) s.relabel_cap = c->rel_cap;
+    s.after_out = end < t_gather || (!fp64 && !relabel && t_items < t_gather);
     return s;
 }
 

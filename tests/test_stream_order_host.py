@@ -105,11 +105,11 @@ def test_second_stream_is_joined_on_errors(stand_in, timing, kernel, call, nth, 
 
 
 @pytest.mark.parametrize("prec,relabel,timing,after_out", [
-    (0, 1, False, False), (0, 0, False, False), (1, 1, False, False), (1, 0, False, True),
+    (0, 1, False, False), (0, 0, False, True), (1, 1, False, False), (1, 0, False, True),
     (0, 1, True, True), (1, 0, True, True)])
 def test_where_the_second_stream_starts(stand_in, prec, relabel, timing, after_out):
-    """With the call; after the OUT elements with timing on, and for limited items
-    alone in the mixed forms (few sub-cell points here: the gather outlasts them)."""
+    """With the call; after the OUT elements with timing on, and where it then ends
+    before the gather (here without the relabel, whose longest element outlasts it)."""
     clean, _, _ = run(stand_in, "", "", 0, timing, prec, relabel)
     side = next(op[1] for op in clean if op[0] == "launch" and op[1] != "10")
     forked = next(i for i, op in enumerate(clean) if op[0] == "wait" and op[1] == side)
